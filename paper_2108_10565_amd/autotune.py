@@ -1,17 +1,18 @@
-"""Autotuner of the fused kernels' tile shape per polynomial degree.
+"""Autotuner of the solve kernel's tile shape per polynomial degree.
 
-The tile shape of degree N is (threads per workgroup, modes per chunk): how
-many elements one workgroup predicts together and how many modes of a degree
-block go through LDS at once.  Both trade occupancy and lane use against
-LDS, registers and how widely the per-element operators and Khat coefficient
-lines are shared, so the best shape is measured, not derived.
+The tile shape of degree N is (waves per workgroup, elements per workgroup,
+modes per chunk, waves per SIMD the registers are held to): how many elements
+one workgroup predicts together, how many modes of a degree block go through
+LDS at once, and how many waves share a SIMD.  They trade occupancy and lane
+use against LDS, registers and how widely Khat is shared, so the best shape is
+measured, not derived.
 
 Two phases, because kernels are compiled on the host and timed on the GPU:
 
     python -m paper_2108_10565_amd.autotune build   [--degrees 3 4 5 6]
         compiles, for every degree and candidate shape, the fused kernels of
         that degree with that shape and links a variant library
-        ``_tune/libstp_N{N}_t{T}_c{C}.so`` (the other degrees and the C ABI
+        ``_tune/libstp_N{N}_{shape}.so`` (the other degrees and the C ABI
         come from the regular build's objects);
 
     python -m paper_2108_10565_amd.autotune measure [--out DIR]
@@ -38,33 +39,27 @@ import time
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 TUNE_DIR = os.path.join(PKG, "_tune")
-CANDIDATES = [(256, 6), (256, 10), (512, 6), (512, 8), (512, 10)]
+CANDIDATES = {0: [(1, 4, 1, 4), (2, 9, 1, 4), (4, 16, 1, 4)],
+              1: [(1, 2, 3, 4), (2, 4, 3, 4), (4, 9, 3, 4)],
+              2: [(1, 1, 6, 4), (2, 3, 3, 4), (2, 3, 6, 5), (4, 6, 6, 4), (5, 8, 6, 4)],
+              3: [(2, 2, 5, 4), (4, 4, 3, 4), (4, 4, 5, 4), (4, 4, 10, 4), (5, 6, 5, 4), (8, 9, 5, 4)],
+              4: [(4, 3, 3, 3), (4, 3, 5, 3), (4, 3, 8, 3), (7, 6, 5, 3), (8, 7, 5, 3), (12, 11, 5, 3)],
+              5: [(4, 3, 2, 3), (4, 3, 3, 3), (4, 3, 5, 2), (8, 6, 5, 2)],
+              6: [(4, 2, 10, 2), (8, 5, 7, 2), (8, 5, 8, 2), (8, 5, 10, 2)],
+              7: [(5, 3, 6, 2), (8, 4, 3, 2), (8, 4, 4, 2)]}
 ELEMENTS = {0: 262144, 1: 262144, 2: 262144, 3: 262144, 4: 262144, 5: 262144, 6: 262144, 7: 65536}
 
 
-def effective(N: int, threads: int, chunk: int):
-    """(threads launched, elements per workgroup, modes per chunk) the kernel
-    derives from a candidate, or None if no element fits."""
-    cols = 13 * (N + 1)
-    elems = min(threads // cols, 16)
-    if elems < 1:
-        return None
-    return ((elems * cols + 63) // 64 * 64, elems, min(chunk, (N + 1) * (N + 2) // 2))
-
-
 def candidates(N: int):
-    """Candidate shapes of degree N, one per distinct effective tile."""
-    seen, out = set(), []
-    for t, c in CANDIDATES:
-        e = effective(N, t, c)
-        if e is not None and e not in seen:
-            seen.add(e)
-            out.append((t, c))
-    return out
+    return CANDIDATES[N]
 
 
-def variant_path(N: int, t: int, c: int) -> str:
-    return os.path.join(TUNE_DIR, f"libstp_N{N}_t{t}_c{c}.so")
+def shape_name(shape) -> str:
+    return "x".join(str(v) for v in shape)
+
+
+def variant_path(N: int, shape) -> str:
+    return os.path.join(TUNE_DIR, f"libstp_N{N}_{shape_name(shape)}.so")
 
 
 def build_variants(degrees, jobs: int | None = None, verbose: bool = True):
@@ -79,28 +74,29 @@ def build_variants(degrees, jobs: int | None = None, verbose: bool = True):
     os.makedirs(tune_obj, exist_ok=True)
     work = []
     for N in degrees:
-        for t, c in candidates(N):
-            work.append((N, t, c, os.path.join(tune_obj, f"kernel_fused_q13_n{N}_t{t}_c{c}.o")))
+        for shape in candidates(N):
+            work.append((N, shape, os.path.join(tune_obj, f"kernel_fused_q13_n{N}_{shape_name(shape)}.o")))
+    tiles = b.tile_table()
 
     def one(item):
-        N, t, c, obj = item
+        N, shape, obj = item
         try:
-            b._run(b.fused_object_cmd(N, t, c, obj, 13))
+            b._run(b.fused_object_cmd(N, tiles[N], shape, obj, 13))
         except RuntimeError as exc:
             return item, str(exc).splitlines()[-1][:200]
         others = [o for o in objs if os.path.basename(o) != b.fused_object_name(13, N)]
-        b._run([b.HIPCC, f"--offload-arch={b.ARCH}", "-shared", "-fPIC", "-o", variant_path(N, t, c)] + others + [obj])
+        b._run([b.HIPCC, f"--offload-arch={b.ARCH}", "-shared", "-fPIC", "-o", variant_path(N, shape)] + others + [obj])
         return item, None
 
     failed = {}
     with cf.ThreadPoolExecutor(max_workers=jobs or min(8, os.cpu_count() or 4)) as ex:
         for item, err in ex.map(one, work):
-            N, t, c, _ = item
+            N, shape, _ = item
             if verbose:
-                print(f"[autotune] N={N} threads={t} chunk={c}: {'built' if err is None else 'skipped: ' + err}",
+                print(f"[autotune] N={N} {shape_name(shape)}: {'built' if err is None else 'skipped: ' + err}",
                       flush=True)
             if err is not None:
-                failed[f"{N}:{t}:{c}"] = err
+                failed[f"{N}:{shape_name(shape)}"] = err
     json.dump({"failed": failed}, open(os.path.join(TUNE_DIR, "build.json"), "w"), indent=1)
     return failed
 
@@ -134,8 +130,8 @@ def measure(degrees, out_dir: str, reps: int = 7, warmup: int = 2):
         stream = torch.cuda.current_stream()
         ref = None
         per = {}
-        for t, c in candidates(N):
-            path = variant_path(N, t, c)
+        for shape in candidates(N):
+            path = variant_path(N, shape)
             if not os.path.exists(path):
                 continue
             lib, h = _load(path)
@@ -168,27 +164,23 @@ def measure(degrees, out_dir: str, reps: int = 7, warmup: int = 2):
             if ref is None:
                 ref = sample
             diff = float(np.linalg.norm(sample - ref) / np.linalg.norm(ref))
-            eff = effective(N, t, c)
-            per[f"{t}x{c}"] = dict(threads=t, chunk=c, threads_launched=eff[0], elements_per_workgroup=eff[1],
-                                   chunk_modes=eff[2], ms_median=float(np.median(ms)), ms_min=float(min(ms)),
-                                   el_per_s=n / (float(np.median(ms)) * 1e-3), rel_diff_vs_first=diff,
-                                   fp32_chain_ms_median=float(np.median(ms32)),
-                                   score_ms=float(np.median(ms)) + float(np.median(ms32)))
-            print(f"[autotune] N={N} n={n} {t}x{c}: float64 {np.median(ms):.3f} ms "
+            per[shape_name(shape)] = dict(shape=list(shape), ms_median=float(np.median(ms)), ms_min=float(min(ms)),
+                                          el_per_s=n / (float(np.median(ms)) * 1e-3), rel_diff_vs_first=diff,
+                                          fp32_chain_ms_median=float(np.median(ms32)),
+                                          score_ms=float(np.median(ms)) + float(np.median(ms32)))
+            print(f"[autotune] N={N} n={n} {shape_name(shape)}: float64 {np.median(ms):.3f} ms "
                   f"({n / np.median(ms) / 1e3:.2f} M el/s), float32 chain {np.median(ms32):.3f} ms, "
                   f"outputs rel diff {diff:.1e}", flush=True)
             if diff > 1e-12:
-                raise RuntimeError(f"variant {t}x{c} of degree {N} computes different outputs ({diff:.2e})")
+                raise RuntimeError(f"variant {shape_name(shape)} of degree {N} computes different outputs ({diff:.2e})")
         best = min(per.values(), key=lambda r: r["score_ms"])
-        results[str(N)] = dict(elements=n, best=[best["threads"], best["chunk"]], candidates=per)
+        results[str(N)] = dict(elements=n, best=best["shape"], candidates=per)
         del dev, Q, Qi
         torch.cuda.empty_cache()
     from . import build as b
     old = json.load(open(b.TILES))
-    tiles = dict(old["tiles"])
-    for N, r in results.items():
-        tiles[N] = r["best"]
-    doc = {"comment": old["comment"], "arch": old.get("arch", "gfx950"), "tiles": tiles,
+    solve = dict(old["solve"], **{"13": dict(old["solve"]["13"], **{N: r["best"] for N, r in results.items()})})
+    doc = {"comment": old["comment"], "arch": old.get("arch", "gfx950"), "tiles": old["tiles"], "solve": solve,
            "measurements": {"device": torch.cuda.get_device_name(0), "date": time.strftime("%Y-%m-%d"),
                             "method": f"float64 stp_predict and the float32 chain (no refinement), median of {reps} "
                                       f"calls after {warmup} warm-ups each, HIP events on one stream; the best shape "
@@ -196,7 +188,7 @@ def measure(degrees, out_dir: str, reps: int = 7, warmup: int = 2):
     os.makedirs(out_dir, exist_ok=True)
     path = os.path.join(out_dir, "tiles.json")
     json.dump(doc, open(path, "w"), indent=1)
-    print(f"[autotune] wrote {path}: {tiles}", flush=True)
+    print(f"[autotune] wrote {path}: {solve}", flush=True)
     return doc
 
 

@@ -60,10 +60,18 @@ TILES = os.path.join(PKG, "tiles.json")
 
 
 def tile_table(path: str = TILES) -> dict:
-    """{degree: (threads, chunk)} of the fused kernels, as the autotuner wrote it."""
+    """{degree: (threads, chunk)} of the residual kernel and the matrix-core chain."""
     import json
     t = json.load(open(path))["tiles"]
     return {int(n): (int(v[0]), int(v[1])) for n, v in t.items()}
+
+
+def solve_table(nq: int, path: str = TILES) -> dict:
+    """{degree: (waves, elements, chunk, waves per SIMD)} of the solve kernel for
+    nq quantities, as the autotuner wrote it."""
+    import json
+    t = json.load(open(path))["solve"][str(nq)]
+    return {int(n): tuple(int(x) for x in v) for n, v in t.items()}
 
 
 # quantity counts with compiled kernels: poroelastic, damped Maxwell
@@ -74,11 +82,14 @@ def fused_object_name(nq: int, n: int) -> str:
     return f"kernel_fused_q{nq}_n{n}.o"
 
 
-def fused_object_cmd(n: int, threads: int, chunk: int, obj: str, nq: int = 13):
+def fused_object_cmd(n: int, tile, solve, obj: str, nq: int = 13):
     """hipcc command compiling the fused kernels of degree n for nq quantities
-    with one tile shape."""
+    with one tile shape (tile: threads, chunk; solve: waves, elements, chunk,
+    waves per SIMD)."""
     return [HIPCC] + HIP_FLAGS + ["-x", "hip", f"-DSTP_NQ={nq}", f"-DSTP_DEGREE={n}",
-                                  f"-DSTP_TILE_THREADS={threads}", f"-DSTP_TILE_CHUNK={chunk}", "-c",
+                                  f"-DSTP_TILE_THREADS={tile[0]}", f"-DSTP_TILE_CHUNK={tile[1]}",
+                                  f"-DSTP_SOLVE_WAVES={solve[0]}", f"-DSTP_SOLVE_ELEMS={solve[1]}",
+                                  f"-DSTP_SOLVE_CHUNK={solve[2]}", f"-DSTP_SOLVE_OCC={solve[3]}", "-c",
                                   os.path.join(CSRC, "kernel_fused.hip"), "-o", obj]
 
 
@@ -90,9 +101,10 @@ def _objects():
         jobs.append(([HIPCC] + HIP_FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", obj], obj))
     tiles = tile_table()
     for nq in QUANTITY_COUNTS:
-        for n in DEGREES:
+        solve = solve_table(nq)
+        for n in sorted(DEGREES, reverse=True):  # the longest compilations first
             obj = os.path.join(BUILD, fused_object_name(nq, n))
-            jobs.append((fused_object_cmd(n, *tiles[n], obj, nq), obj))
+            jobs.append((fused_object_cmd(n, tiles[n], solve[n], obj, nq), obj))
     return jobs
 
 

@@ -1,39 +1,31 @@
-// Fused, register-resident kernel for Algorithm 3 of Wolf et al. (arXiv
-// 2108.10565, section "Block-wise back-substitution"), one object per degree
-// N = STP_DEGREE.
+// Register-resident kernels for Algorithm 3 of Wolf et al. (arXiv 2108.10565,
+// section "Block-wise back-substitution"), one object per quantity count and
+// degree N = STP_DEGREE: the solve (solve_kernel.hpp), the float32 chain on
+// the matrix cores, and the float64 residual of the mixed-precision path.
 //
-// Mapping.  One lane per column (element e, quantity p, time mode u) of the
-// element's right-hand side b_pmu (eq:b_pmu); kNQ (N+1) lanes per element,
-// kElems elements per workgroup (512 lanes at most), lanes ordered
-// quantity-major.
-// Every lane keeps b[m] for all modes m below the top degree block in
-// registers.  The green-block update
+// Shared structure.  One lane per column (element e, quantity p, time mode u)
+// of the element's right-hand side b_pmu (eq:b_pmu), which keeps b[m] for all
+// modes m below the top degree block in registers.  The green-block update
 //     b[p, n, u] -= sum_j Khat^j[n, m] (A^{j*} X[:, m, u])_p ,  n < block_start(g)
 // is lane-local once the star product y_j = (A^{j*} X[:, m, u])_p is known,
-// so the lane applies it as a fully unrolled list of fused multiply-adds
-// over the non-zeros of Khat (compile-time pattern, coefficients read with
-// scalar loads from a device table), exactly the zeros the Lemma of section
-// "Structure of the system matrix" and the Dubiner structure provide.
+// so the lane applies it as a fully unrolled list of multiply-adds over the
+// non-zeros of Khat (compile-time pattern), exactly the zeros the Lemma of
+// section "Structure of the system matrix" and the Dubiner structure provide.
 //
-// Per chunk of up to kChunkMax modes m of degree block g (g = N .. 0):
-//   1. every lane writes b[m] to LDS (top block: b = Q0 (S^-1 w), eq:b_pmu);
-//   2. dark-blue blocks and G coupling: lane (e, p, s) forms X[p, m, s] =
-//      row s of (Z - E*_pp I)^-1 times b[p, m, :] (float64).  For E*_pp = 0
-//      that row is a row of Z^-1, which is tridiagonal with a zero diagonal
-//      apart from its two corner entries (the Legendre integration
-//      recurrence), so such lanes read two entries of b instead of T; the
-//      dense rows are read only by waves holding a lane that needs them.
-//      A quantity o whose row of the strict upper part G of E* holds one
-//      coupling G_op to an uncoupled quantity p (the poroelastic u <- uf,
-//      v <- vf, w <- wf) uses the closed form
+// Per chunk of modes m of degree block g (g = N .. 0):
+//   1. dark-blue blocks and G coupling: X[p, m, s] = row s of
+//      (Z - E*_pp I)^-1 times b[p, m, :] (float64).  For E*_pp = 0 that row is
+//      a row of Z^-1, which is tridiagonal with a zero diagonal apart from its
+//      two corner entries (the Legendre integration recurrence): two entries
+//      instead of T.  A quantity o whose row of the strict upper part G of E*
+//      holds one coupling G_op to an uncoupled quantity p (the poroelastic
+//      u <- uf, v <- vf, w <- wf) uses the closed form
 //      X_o = Zinv_o (b_o + G_op X_p) = zr . b_o + dr . b_p,
 //      dr = G_op (row of Zinv_o) Zinv_p, so no extra round is needed; any
 //      other upper-triangular E is handled level by level (level = longest
 //      coupling chain below a quantity);
-//   3. X of the chunk goes from LDS to Q (and dt X[:, :, 0] to Qint) in
-//      contiguous runs, with streaming stores issued before and early in
-//      step 4;
-//   4. green blocks: every lane reads X[q, m, u] of the quantities in its
+//   2. outputs: X to Q and dt X[:, :, 0] to Qint;
+//   3. green blocks: every lane reads X[q, m, u] of the quantities in its
 //      star row, forms y_1..y_3 with its row of A^{1*}, A^{2*}, A^{3*}, and
 //      subtracts Khat^j[n, m] y_j from its registers b[n].
 // A^{j*} = dt A^j and E* = dt E are formed in-kernel, so every product runs
@@ -448,11 +440,15 @@ __host__ __device__ constexpr int chunk_index(int N, int g, int ci, int cmax) {
 __host__ __device__ constexpr int next_block(int g, int ci, int cmax) { return ci + 1 < nchunks(g, cmax) ? g : g - 1; }
 __host__ __device__ constexpr int next_chunk(int g, int ci, int cmax) { return ci + 1 < nchunks(g, cmax) ? ci + 1 : 0; }
 
-// Modes of the solve kernel.
-constexpr int kInit = 0;     // b = Q0 (S^-1 w); Q <- X
-constexpr int kCorrect = 1;  // b = residual (float workspace); Q <- Q + X
+}  // namespace
+}  // namespace stp
 
-// Per-lane setup shared by the solve and residual kernels: stages E* and
+#include "solve_kernel.hpp"
+
+namespace stp {
+namespace {
+
+// Per-lane setup shared by the matrix-core chain and the residual kernel: stages E* and
 // A^{j*} of the group, then per lane the sparse star row, the G coupling of
 // the lane's quantity, row u of (Z - E*_pp I)^-1 (to LDS) and the closure row
 // dr (to LDS); the dependency levels of the strict upper part G of E* only
@@ -462,10 +458,6 @@ struct LaneSetup {
   using C = Cfg<N>;
   R sa0[kStarNnz], sa1[kStarNnz], sa2[kStarNnz];
   int sq[kStarNnz];
-  // LDS addresses of the star-row entries in one fixed chunk buffer (bind):
-  // the reads of each mode then take the mode's offset as an immediate
-  using LdsR = __attribute__((address_space(3))) const R;
-  LdsR* sp[kStarNnz];
   int gp, gcount;
   double gcoef;
   bool dense_star, closure;
@@ -636,29 +628,6 @@ struct LaneSetup {
     }
   }
 
-  __device__ __forceinline__ void bind(const R* buf) {
-#pragma unroll
-    for (int k = 0; k < kStarNnz; ++k) sp[k] = (LdsR*)buf + sq[k];
-  }
-  // star() for the buffer given to bind(): no address arithmetic per mode
-  template <int kk>
-  __device__ __forceinline__ void star_bound(const R* bufX, const PredictArgs& a, int64_t e0, int es, int p, int u,
-                                             bool active, R& y0, R& y1, R& y2) const {
-    constexpr int T = C::T;
-    y0 = y1 = y2 = R(0);
-    if (!dense_star) {
-#pragma unroll
-      for (int k = 0; k < kStarNnz; ++k) {
-        const R xq = sp[k][kk * T];
-        y0 = fma(sa0[k], xq, y0);
-        y1 = fma(sa1[k], xq, y1);
-        y2 = fma(sa2[k], xq, y2);
-      }
-    } else {
-      star<kk>(bufX, a, e0, es, p, u, active, y0, y1, y2);
-    }
-  }
-
   // y_j = (A^{j*} X[:, m, u])_p for j = 1..3 from the chunk buffer
   template <int kk>
   __device__ __forceinline__ void star(const R* bufX, const PredictArgs& a, int64_t e0, int es, int p, int u,
@@ -689,321 +658,6 @@ struct LaneSetup {
     }
   }
 };
-
-// Algorithm 3 over a group of elements in precision R (the dark-blue solves
-// are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
-// b = the residual in `rin` (float), Q <- Q + X.
-template <int N, typename R, int Mode>
-__global__ __launch_bounds__(Cfg<N>::kThreads) void fused_solve_kernel(PredictArgs a, const float* rin) {
-  using C = Cfg<N>;
-  constexpr int B = C::B, T = C::T, kE = C::kElems, kThreads = C::kThreads;
-  __shared__ Shared<N, R> sh;
-  R* const bufB = sh.u.c.bufB;
-  R* const bufX = sh.u.c.bufX;
-  const int tid = threadIdx.x;
-  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kE;
-  const int64_t nloc64 = a.n - e0 < kE ? a.n - e0 : kE;
-  const int nloc = static_cast<int>(nloc64);
-  const LaneId<N> lid(tid);
-  const int es = lid.es, p = lid.p, u = lid.u;
-  const bool active = es < nloc;
-  const int cb = C::blk(es, p);  // this lane's (element, quantity) block in bufB / bufX
-  const R* kv = khat_sparse<N, R>();
-  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int64_t erow = ((active ? e0 + es : 0) * kNQ + p);  // (element, quantity) row of this lane
-
-  // register rows of b below the top block, loaded after the per-element
-  // setup (so that its loads do not wait behind them and its elimination
-  // does not compete with them for registers); the float64 rows are scaled
-  // just before the first green update, when they have arrived.
-  constexpr bool kDeferRows = Mode == kInit && std::is_same_v<R, double>;
-  R b[C::LR];
-  const double w_u = sinv_w(u);
-  const double* const q0row = a.Q0 + erow * B;
-  // Q0 of the first chunk (top block): its loads are issued before the
-  // per-element setup so that their latency overlaps it; the registers then
-  // carry each following top-block chunk, loaded one chunk ahead
-  constexpr int kFirstC = chunk_size(N, C::kChunk, 0), kFirstM = chunk_start(N, C::kChunk, 0);
-  constexpr int kFirstPer = (kE * kNQ * kFirstC + kThreads - 1) / kThreads;
-  double q_first[kFirstPer];
-  if constexpr (Mode == kInit) {
-#pragma unroll
-    for (int k = 0; k < kFirstPer; ++k) {
-      const int i = tid + k * kThreads;
-      const int ee = i / (kNQ * kFirstC), pp = (i / kFirstC) % kNQ, kk = i % kFirstC;
-      q_first[k] = (ee < nloc) ? a.Q0[((e0 + ee) * kNQ + pp) * B + kFirstM + kk] : 0.0;
-    }
-  }
-  LaneSetup<N, R> L;
-  L.run(sh, a, e0, nloc, tid, es, p, u, active, cb);
-  if constexpr (kDeferRows) {
-#pragma unroll
-    for (int n = 0; n < C::LN; ++n) b[n] = q0row[n];
-  } else if constexpr (Mode == kInit) {
-    // b[p, n, u] = Q0[p, n] (S^-1 w)_u (eq:b_pmu), converted on arrival
-#pragma unroll
-    for (int n = 0; n < C::LN; ++n) b[n] = static_cast<R>(q0row[n] * w_u);
-  } else if constexpr (Mode == kCorrect) {
-    // the residual rows below the top block (after the setup, like the rows
-    // of the float64 solve)
-    const float* rrow = rin + erow * (B * T) + u;
-#pragma unroll
-    for (int n = 0; n < C::LN; ++n) b[n] = static_cast<R>(rrow[n * T]);
-  }
-  const int pb = C::blk(es, L.gp);  // block of the coupled quantity (own block if uncoupled)
-  L.bind(bufX);
-  // Quantities without a diagonal source (E*_pp = 0) solve with Z^-1, whose
-  // rows have two non-zeros (columns zc0, zc1 of row u); the dense row u of
-  // (Z - E*_pp I)^-1 and the closure row dr are read only by waves holding a
-  // lane that needs them (wave-uniform flags, scalar branches).
-  using ZS = stp_gen::ZinvSparse<N>;
-  const int cz0 = cb + ZS::col[2 * u], cz1 = cb + ZS::col[2 * u + 1];
-  const double zv0 = ZS::val[2 * u], zv1 = ZS::val[2 * u + 1];
-  const bool wave_stiff = __builtin_amdgcn_ballot_w64(sh.G[es][p][p] != 0.0) != 0;
-  const bool wave_coupled = __builtin_amdgcn_ballot_w64(L.gcount == 1) != 0;
-
-  static_for<0, N + 1>([&](auto gi) __attribute__((always_inline)) {
-    constexpr int g = N - decltype(gi)::value;
-    static_for<0, nchunks(g, C::kChunk)>([&](auto ci) __attribute__((always_inline)) {
-      constexpr int m0 = chunk_start(g, C::kChunk, decltype(ci)::value);
-      constexpr int c = chunk_size(g, C::kChunk, decltype(ci)::value);
-      constexpr int kOut = (kE * kNQ * c * T + kThreads - 1) / kThreads;  // output values per lane
-      // kCorrect: the previous Q of this lane's output values, loaded at the
-      // start of the chunk so that the latency overlaps steps 1 and 2
-      double qpre[Mode == kCorrect ? kOut : 1];
-      if constexpr (Mode == kCorrect) {
-        constexpr int per = c * T;
-#pragma unroll
-        for (int k = 0; k < kOut; ++k) {
-          const int i = tid + k * kThreads;
-          qpre[k] = i < nloc * kNQ * per ? a.Q[(e0 * kNQ + i / per) * (B * T) + m0 * T + i % per] : 0.0;
-        }
-      }
-      if constexpr (g > 0) prefetch_columns<N, R, m0, c, kThreads / 64>(kv, wave);
-      // 1. right-hand side of the chunk to LDS; the top block has received no
-      //    update yet, so it comes straight from memory
-      if constexpr (g == N) {
-        if constexpr (Mode == kInit) {
-          constexpr int per_thread = (kE * kNQ * c + kThreads - 1) / kThreads;
-          double q[per_thread];
-          // chunk 0 was loaded before the setup, the others during the green
-          // update of the chunk before them
-          static_assert(per_thread <= kFirstPer && (decltype(ci)::value > 0 || m0 == kFirstM), "top chunks");
-#pragma unroll
-          for (int k = 0; k < per_thread; ++k) q[k] = q_first[k];
-#pragma unroll
-          for (int k = 0; k < per_thread; ++k) {
-            const int i = tid + k * kThreads;
-            const int ee = i / (kNQ * c), pp = (i / c) % kNQ, kk = i % c;
-            if (ee < nloc) {
-#pragma unroll
-              for (int uu = 0; uu < T; ++uu)
-                bufB[C::blk(ee, pp) + kk * T + uu] = static_cast<R>(q[k] * sinv_w(uu));
-            }
-          }
-        } else {
-          stage_rows<N, R, c * T>(bufB, rin, e0, m0 * T, nloc, tid);
-        }
-      } else {
-        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-          bufB[cb + decltype(k)::value * T + u] = b[m0 + decltype(k)::value];
-        });
-      }
-      __syncthreads();
-      // 2. dark-blue blocks and G coupling (float64)
-      if (L.closure) {
-        // One straight-line variant per combination of the wave-uniform
-        // flags, so that the LDS reads of all modes of the chunk can be in
-        // flight together.
-        auto dark_blue = [&](auto stiff_c, auto coupled_c) __attribute__((always_inline)) {
-          constexpr bool kStiff = decltype(stiff_c)::value, kCoupled = decltype(coupled_c)::value;
-          double zr[T], drr[T];
-          if constexpr (kStiff) {
-#pragma unroll
-            for (int v = 0; v < T; ++v) zr[v] = sh.zr[tid][v];
-          }
-          if constexpr (kCoupled) {
-#pragma unroll
-            for (int v = 0; v < T; ++v) drr[v] = sh.dr[tid][v];
-          }
-          static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-            constexpr int kk = decltype(k)::value;
-            double x;
-            if constexpr (kStiff) {
-              // dense row u of (Z - E*_pp I)^-1 (Z^-1 for the lanes without
-              // a diagonal source in this wave)
-              x = 0.0;
-#pragma unroll
-              for (int v = 0; v < T; ++v) x = fma(zr[v], static_cast<double>(bufB[cb + kk * T + v]), x);
-            } else {
-              x = fma(zv0, static_cast<double>(bufB[cz0 + kk * T]), zv1 * static_cast<double>(bufB[cz1 + kk * T]));
-            }
-            if constexpr (kCoupled) {
-              // closure coupling dr . b_p (dr = 0 in uncoupled lanes)
-#pragma unroll
-              for (int v = 0; v < T; ++v) x = fma(drr[v], static_cast<double>(bufB[pb + kk * T + v]), x);
-            }
-            bufX[cb + kk * T + u] = static_cast<R>(x);
-          });
-        };
-        using yes = std::true_type;
-        using no = std::false_type;
-        if (wave_stiff) {
-          if (wave_coupled) dark_blue(yes{}, yes{});
-          else dark_blue(yes{}, no{});
-        } else {
-          if (wave_coupled) dark_blue(no{}, yes{});
-          else dark_blue(no{}, no{});
-        }
-      } else {
-        double zr[T];
-#pragma unroll
-        for (int v = 0; v < T; ++v) zr[v] = sh.zr[tid][v];
-        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-          constexpr int kk = decltype(k)::value;
-          double x = 0.0;
-#pragma unroll
-          for (int v = 0; v < T; ++v) x = fma(zr[v], static_cast<double>(bufB[cb + kk * T + v]), x);
-          bufX[cb + kk * T + u] = static_cast<R>(x);
-        });
-        // general upper-triangular E: level by level, each level after the
-        // levels it depends on
-        for (int r = 1; r <= L.maxlevel; ++r) {
-          __syncthreads();
-          if (L.mylevel == r) {
-            static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-              constexpr int kk = decltype(k)::value;
-              double acc[T];
-#pragma unroll
-              for (int v = 0; v < T; ++v) acc[v] = static_cast<double>(bufB[cb + kk * T + v]);
-              for (int q = p + 1; q < kNQ; ++q) {
-                const double gq = sh.G[es][p][q];
-                if (gq != 0.0) {
-                  const int qb = C::blk(es, q) + kk * T;
-#pragma unroll
-                  for (int v = 0; v < T; ++v) acc[v] = fma(gq, static_cast<double>(bufX[qb + v]), acc[v]);
-                }
-              }
-              double x = 0.0;
-#pragma unroll
-              for (int v = 0; v < T; ++v) x = fma(zr[v], acc[v], x);
-              bufX[cb + kk * T + u] = static_cast<R>(x);
-            });
-          }
-        }
-      }
-      __syncthreads();
-      // 3. outputs of the chunk from the X buffer: every (element, quantity)
-      //    row of the chunk is one contiguous run of c*T doubles of Q, so
-      //    consecutive lanes store consecutive doubles.  Each lane stores
-      //    kOut values: kInit in nOut groups of kOutGroup (LDS reads issued
-      //    before the stores) in a rolled loop, which keeps the registers of
-      //    this step few; kCorrect adds the previous Q loaded at the start of
-      //    the chunk, in one unrolled pass.  The streaming stores drain while
-      //    the green update computes: kInit issues a quarter of its groups
-      //    here and the rest after the first quarter of the chunk's green
-      //    modes (measured ~1% faster at N=6 than issuing all of them here,
-      //    where the burst waits on the compute unit's write queue).
-      //    Q <- X (kInit) or Q <- Q + X (kCorrect); then Qint = dt X[:, :, 0]
-      //    in its own pass (consecutive lanes, consecutive modes), so no store
-      //    instruction runs with one lane in T.  The block stays open over
-      //    step 4, which issues the remaining kInit groups.
-      {
-        constexpr int per = c * T;
-        constexpr int kOutGroup = 3;
-        constexpr int nOut = (kOut + kOutGroup - 1) / kOutGroup;
-        constexpr int kOutEarly = (g > 0) ? (nOut + 3) / 4 : nOut;   // groups issued before step 4
-        const int limit = nloc * kNQ * per;
-        double* Qg = a.Q + e0 * (kNQ * B * T) + m0 * T;
-        // value k of this lane: run index i = tid + k kThreads -> (row, r)
-        auto lds_index = [&](int i) __attribute__((always_inline)) { return C::rowblk(i / per) + i % per; };
-        // streaming stores: Q is written once and not read again here, so
-        // it should not displace the Khat lines in L2
-        auto store_groups = [&](int glo, int ghi) __attribute__((always_inline)) {
-#pragma unroll 1
-          for (int gi = glo; gi < ghi; ++gi) {
-            double xv[kOutGroup];
-#pragma unroll
-            for (int k = 0; k < kOutGroup; ++k)
-              xv[k] = static_cast<double>(bufX[lds_index(tid + (gi * kOutGroup + k) * kThreads)]);
-#pragma unroll
-            for (int k = 0; k < kOutGroup; ++k) {
-              const int i = tid + (gi * kOutGroup + k) * kThreads;
-              if (i < limit) __builtin_nontemporal_store(xv[k], &Qg[(i / per) * (B * T) + i % per]);
-            }
-          }
-        };
-        if constexpr (Mode == kInit) {
-          store_groups(0, kOutEarly);
-        } else {
-          double xv[kOut];
-#pragma unroll
-          for (int k = 0; k < kOut; ++k) xv[k] = static_cast<double>(bufX[lds_index(tid + k * kThreads)]);
-#pragma unroll
-          for (int k = 0; k < kOut; ++k) {
-            const int i = tid + k * kThreads;
-            if (i < limit) __builtin_nontemporal_store(xv[k] + qpre[k], &Qg[(i / per) * (B * T) + i % per]);
-          }
-        }
-        // Qint of the chunk: c contiguous values per (element, quantity) row.
-        // kCorrect adds dt X to the previous Qint (read and written by the
-        // same lane; Q itself is being rewritten by other lanes above).
-        if (a.Qint) {
-          double* Ig = a.Qint + e0 * (kNQ * B);
-          constexpr int kInt = (kE * kNQ * c + kThreads - 1) / kThreads;
-          const int ilimit = nloc * kNQ * c;
-#pragma unroll
-          for (int k = 0; k < kInt; ++k) {
-            const int j = tid + k * kThreads;
-            const int row = j / c, kk = j % c;
-            double v = a.dt * static_cast<double>(bufX[C::rowblk(row) + kk * T]);
-            if constexpr (Mode == kCorrect) v += j < ilimit ? Ig[row * B + m0 + kk] : 0.0;
-            if (j < ilimit) __builtin_nontemporal_store(v, &Ig[row * B + m0 + kk]);
-          }
-        }
-      // 4. green blocks (lane-local): star product, then Khat columns.  X of
-      //    the chunk stays in bufX until the next chunk's step 2, so the
-      //    remaining output groups are read from it here.
-      if constexpr (g > 0) {
-        if constexpr (kDeferRows && g == N && decltype(ci)::value == 0) {
-          // b[p, n, u] = Q0[p, n] (S^-1 w)_u (eq:b_pmu)
-#pragma unroll
-          for (int n = 0; n < C::LN; ++n) b[n] *= w_u;
-        }
-        if constexpr (Mode == kInit && g == N && decltype(ci)::value + 1 < nchunks(N, C::kChunk)) {
-          // Q0 of the next top-block chunk, in flight during this green update
-          constexpr int cn = chunk_size(N, C::kChunk, decltype(ci)::value + 1);
-          constexpr int mn = chunk_start(N, C::kChunk, decltype(ci)::value + 1);
-          constexpr int per_next = (kE * kNQ * cn + kThreads - 1) / kThreads;
-#pragma unroll
-          for (int k = 0; k < per_next; ++k) {
-            const int i = tid + k * kThreads;
-            const int ee = i / (kNQ * cn), pp = (i / cn) % kNQ, kk = i % cn;
-            q_first[k] = (ee < nloc) ? a.Q0[((e0 + ee) * kNQ + pp) * B + mn + kk] : 0.0;
-          }
-        }
-        R kgrp[kGroup<R>];
-        load_first_group<N, m0, R>(kv, kgrp);
-        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-          constexpr int kk = decltype(k)::value;
-          if constexpr (Mode == kInit && kk == c / 4) {
-            store_groups(kOutEarly, nOut);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          R y0, y1, y2;
-          // the star reads take the mode offset as an immediate (measured
-          // 2.3% faster in float64 and 4% in the float chain; the residual
-          // kernel, whose chunk buffer alternates, keeps the per-mode form)
-          L.template star_bound<kk>(bufX, a, e0, es, p, u, active, y0, y1, y2);
-          green_column<N, m0 + kk, (kk + 1 < c ? m0 + kk + 1 : -1), R>(b, y0, y1, y2, kv, kgrp);
-          // keep the scheduler from hoisting the next mode's LDS reads
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      }
-      }  // output block of step 3
-    });
-  });
-}
 
 // ---------------------------------------------------------------------------
 // Float32 chain with the green-block update on the matrix cores.
@@ -1531,25 +1185,26 @@ hipError_t launch_fused<STP_NQ, STP_DEGREE>(const PredictArgs& a, int precision,
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(groups)), block(C::kThreads);
   if (precision == 0) {
-    hipLaunchKernelGGL((fused_solve_kernel<N, double, kInit>), grid, block, 0, stream, a, nullptr);
-    return hipGetLastError();
+    return launch_solve<N, double, kInit>(a, nullptr, stream);
   }
-  if (valu_float_chain)
-    hipLaunchKernelGGL((fused_solve_kernel<N, float, kInit>), grid, block, 0, stream, a, nullptr);
-  else
+  hipError_t err;
+  if (valu_float_chain) {
+    err = launch_solve<N, float, kInit>(a, nullptr, stream);
+  } else {
     hipLaunchKernelGGL((mfma_solve_kernel<N, kInit>), grid, block, 0, stream, a, nullptr);
-  hipError_t err = hipGetLastError();
+    err = hipGetLastError();
+  }
   for (int k = 0; k < refine_steps && err == hipSuccess; ++k) {
     hipLaunchKernelGGL((fused_residual_kernel<N>), grid, block, 0, stream, a, workspace);
     err = hipGetLastError();
     if (err != hipSuccess) break;
-    if (valu_float_chain)
-      hipLaunchKernelGGL((fused_solve_kernel<N, float, kCorrect>), grid, block, 0, stream, a,
-                         static_cast<const float*>(workspace));
-    else
+    if (valu_float_chain) {
+      err = launch_solve<N, float, kCorrect>(a, workspace, stream);
+    } else {
       hipLaunchKernelGGL((mfma_solve_kernel<N, kCorrect>), grid, block, 0, stream, a,
                          static_cast<const float*>(workspace));
-    err = hipGetLastError();
+      err = hipGetLastError();
+    }
   }
   return err;
 }

@@ -1,0 +1,702 @@
+// The fused solve of Algorithm 3 (section "Block-wise back-substitution" of
+// Wolf et al., arXiv 2108.10565): float64 predictor, float32 chain and
+// float32 correction, included by the per-degree object.
+//
+// What bounds it.  At N = 6 an element needs 1.0 MFLOP on the float64 vector
+// pipe (14.6 ns at the measured 70 TFLOP/s) and moves 84 KB (16.8 ns at the
+// measured 5 TB/s copy), so neither alone explains 50 ns: with one or two
+// waves per SIMD the time goes to latencies that nothing overlaps (scalar
+// loads of Khat, workgroup barriers, LDS round trips of the dark-blue step).
+// The layout below is chosen to remove those:
+//
+// * Columns.  One lane per right-hand-side column (element e, quantity p,
+//   time mode u).  A wave holds whole (e, p) groups of T = N + 1 lanes,
+//   floor(64 / T) of them (63 of 64 lanes at T = 7), and a coupled quantity
+//   shares its wave with its partner (the poroelastic u, v, w <- uf, vf, wf).
+//   The dark-blue step and the G coupling therefore exchange data inside one
+//   wave, through LDS but without a workgroup barrier, and every chunk needs
+//   a single barrier: between its X and the star products that read X of the
+//   other quantities.  X alternates between two buffers.
+// * Khat.  The coefficients sit in LDS in usage order; one read brings 16 of
+//   them into one register pair (lane l holds coefficient l mod 16) and each
+//   multiply-add picks its own with a row broadcast (DPP row_newbcast), at
+//   the full float64 rate (measured 76 TFLOP/s against 72 with scalar
+//   operands).  Scalar loads, used before, can only be waited for all
+//   together, which exposed their latency once per 8 multiply-adds: the
+//   green update ran at half the pipe rate.  LDS reads are waited for in
+//   order, so two groups stay in flight.
+// * Top block.  b = Q0 (S^-1 w) there, so X = Q0 (row of Zinv . S^-1 w) (and
+//   the same product with the closure row for a coupled quantity) is one or
+//   two products per value, without an exchange.
+// * Outputs.  A group's lanes store pairs of consecutive doubles of its own
+//   row (16 bytes per lane, T lanes contiguous): no index arithmetic, any
+//   chunk size.  Ordinary stores: streaming stores of these 112-byte pieces
+//   reach HBM as partial lines (N = 6: 4.08 ms against 2.98 ms).
+// * Workgroups are small where the degree's registers allow several per
+//   compute unit, so that one group's setup and barriers overlap another's
+//   multiply-adds (the tile table of the build).
+//
+// Inputs outside the fast forms take general code in the same kernel, chosen
+// per workgroup: a star row with more than kStarNnz columns reads the dense
+// rows from memory, and an E whose couplings are not of the closure form (or
+// whose partner sits in another wave) is solved level by level with a
+// barrier per level.
+#pragma once
+
+// Tile of this degree: waves and elements per workgroup, modes per chunk,
+// waves per SIMD the registers are held to.
+#if !defined(STP_SOLVE_WAVES) || !defined(STP_SOLVE_ELEMS) || !defined(STP_SOLVE_CHUNK) || !defined(STP_SOLVE_OCC)
+#error "compile with the solve tile of the build's table"
+#endif
+
+namespace stp {
+namespace {
+
+template <int N>
+struct SolveCfg {
+  static constexpr int B = n_modes(N), T = N + 1;
+  static constexpr int LN = block_start(N);        // register-resident rows (below the top block)
+  static constexpr int LR = LN > 0 ? LN : 1;
+  static constexpr int DN = block_size(N);
+  static constexpr int kWaves = STP_SOLVE_WAVES, kThreads = 64 * kWaves, kE = STP_SOLVE_ELEMS;
+  static constexpr int GW = 64 / T;                // groups of T lanes per wave
+  static constexpr int kPos = kWaves * GW;         // group positions of the workgroup
+  static constexpr int kRows = kE * kNQ;           // (element, quantity) rows
+  static_assert(kRows <= kPos, "the elements must fit the workgroup's positions");
+  static constexpr int kChunk = STP_SOLVE_CHUNK < DN ? STP_SOLVE_CHUNK : DN;
+  // X buffers: one block of S values per position.  S = T mod 16, so that the
+  // address of lane (position, u) is congruent to T position + u: consecutive
+  // lanes of a wave fall on consecutive banks.
+  static constexpr int stride() {
+    int s = kChunk * T;
+    while ((s - T) % 16 != 0) ++s;
+    return s;
+  }
+  static constexpr int S = stride();
+  static constexpr int kBuf = (kPos + 1) * S;      // + one block for the lanes past the last group
+};
+
+// Which row (element * kNQ + quantity) each position holds, and back.  A
+// position without a row is -1.  Poroelastic rows are grouped by the length
+// of their star row, which is uniform over most waves that way: normal
+// stresses and pressure (6 columns), then the velocity pairs (4; a pair never
+// straddles two waves, a shear row fills the gap), then the shear stresses
+// (2).
+template <int N>
+struct SolveLayout {
+  using C = SolveCfg<N>;
+  short row[C::kPos];
+  short pos[C::kRows];
+  constexpr SolveLayout() : row(), pos() {
+    for (int i = 0; i < C::kPos; ++i) row[i] = -1;
+    int next = 0;
+    if (kNQ == kNQPoro) {
+      const int wide[4] = {0, 1, 2, 9}, shear[3] = {3, 4, 5};
+      int filled = 0;  // shear rows placed so far
+      for (int k = 0; k < 4; ++k)
+        for (int e = 0; e < C::kE; ++e) row[next++] = static_cast<short>(e * kNQ + wide[k]);
+      for (int k = 0; k < 3; ++k)
+        for (int e = 0; e < C::kE; ++e) {
+          if (C::GW > 1 && next % C::GW == C::GW - 1) {
+            if (filled < 3 * C::kE) {
+              row[next] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
+              ++filled;
+            }
+            ++next;
+          }
+          row[next++] = static_cast<short>(e * kNQ + 6 + k);
+          row[next++] = static_cast<short>(e * kNQ + 10 + k);
+        }
+      for (; filled < 3 * C::kE; ++filled)
+        row[next++] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
+    } else {
+      for (int q = 0; q < kNQ; ++q)
+        for (int e = 0; e < C::kE; ++e) row[next++] = static_cast<short>(e * kNQ + q);
+    }
+    for (int i = 0; i < C::kPos; ++i)
+      if (row[i] >= 0) pos[row[i]] = static_cast<short>(i);
+  }
+};
+template <int N>
+__device__ const SolveLayout<N> kSolveLayout{};
+
+template <int N>
+constexpr int khat_nnz() {
+  using P = stp_gen::KhatPattern<N>;
+  int n = 0;
+  for (int m = 0; m < SolveCfg<N>::B; ++m)
+    n = P::col_start[m] + P::col_count[m] > n ? P::col_start[m] + P::col_count[m] : n;
+  return n;
+}
+
+template <int N, typename R>
+struct SolveShared {
+  using C = SolveCfg<N>;
+  static constexpr int kTab = (khat_nnz<N>() + 15) / 16 * 16;
+  R khat[kTab > 0 ? kTab : 16];            // Khat in usage order
+  double rows[C::kThreads][C::T];          // per lane: dense row of its dark-blue step
+  double q0[(C::kPos + 1) * C::DN];        // Q0 of the top block
+  int pos[C::kRows];
+  int row[C::kPos + 1];                    // of a position (the general code's; -1: none)
+  int level[C::kRows];
+  int maxlevel;
+  unsigned flags;
+  union {
+    struct {                               // setup only
+      double G[C::kE][kNQ][kNQ];           // E* (lower part zeroed)
+      double A[C::kE][3][kNQ][kNQ];        // -A^{j*}: the green update then adds Khat y
+    } s;
+    R x[2 * C::kBuf + 2 * C::T * C::T];    // X of two chunks (+ what the last lanes' output reads may run over)
+  } u;
+};
+
+// b += coefficient I of the 16 that the wave's register k holds, times y
+// (v_fmac with a row broadcast; k comes straight from an LDS read, so the
+// broadcast never follows a vector write of k).
+template <int I>
+__device__ __forceinline__ void fmac_bcast(double& b, double k, double y) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(b) : "v"(k), "v"(y), "n"(I));
+}
+template <int I>
+__device__ __forceinline__ void fmac_bcast(float& b, float k, float y) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(b) : "v"(k), "v"(y), "n"(I));
+}
+
+// The columns of the two-entry rows of Z^-1 (generated) are max(u - 1, 0) and
+// min(u + 1, N).
+template <int N>
+constexpr bool zinv_columns() {
+  using ZS = stp_gen::ZinvSparse<N>;
+  for (int u = 0; u <= N; ++u) {
+    if (ZS::col[2 * u] != (u > 0 ? u - 1 : 0) && ZS::val[2 * u] != 0.0) return false;
+    if (ZS::col[2 * u + 1] != (u < N ? u + 1 : N) && ZS::val[2 * u + 1] != 0.0) return false;
+  }
+  return true;
+}
+
+// Orders the LDS accesses of one wave (a wave's LDS operations complete in
+// order; this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+
+constexpr int kInit = 0;     // b = Q0 (S^-1 w); Q <- X
+constexpr int kCorrect = 1;  // b = residual (float workspace); Q <- Q + X
+
+constexpr unsigned kDenseStar = 1u, kGeneralE = 2u;
+
+// Algorithm 3 over a group of elements in precision R (the dark-blue solves
+// are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
+// b = the residual in `rin` (float), Q <- Q + X.
+template <int N, typename R, int Mode>
+__global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_kernel(PredictArgs a, const float* rin) {
+  using C = SolveCfg<N>;
+  using P = stp_gen::KhatPattern<N>;
+  using ZS = stp_gen::ZinvSparse<N>;
+  using LdsR = __attribute__((address_space(3))) R;
+  using LdsD = __attribute__((address_space(3))) double;
+  constexpr int B = C::B, T = C::T, kE = C::kE, kThreads = C::kThreads, S = C::S, GW = C::GW, DN = C::DN, LN = C::LN;
+  static_assert(zinv_columns<N>(), "two-entry rows of Z^-1");
+  __shared__ SolveShared<N, R> sh;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kE;
+  const int64_t nloc64 = a.n - e0 < kE ? a.n - e0 : kE;
+  const int nloc = static_cast<int>(nloc64);
+  const int grp = lane / T, u = lane - grp * T;
+  const int pos = grp < GW ? wave * GW + grp : C::kPos;
+  const int row = grp < GW ? kSolveLayout<N>.row[pos] : -1;
+
+  // ---- setup: E, star and Khat to LDS (every load issued before the first
+  // LDS store, so the group waits for one memory latency)
+  constexpr int kEIt = (kE * kNQ * kNQ + kThreads - 1) / kThreads;
+  constexpr int kAIt = (3 * kE * kNQ * kNQ + kThreads - 1) / kThreads;
+  constexpr int nnz = khat_nnz<N>(), kTab = SolveShared<N, R>::kTab, kKIt = (kTab + kThreads - 1) / kThreads;
+  {
+    double ev[kEIt], av[kAIt];
+    R kv[kKIt > 0 ? kKIt : 1];
+    const R* const ktab = khat_sparse<N, R>();
+#pragma unroll
+    for (int k = 0; k < kEIt; ++k) {
+      const int i = tid + k * kThreads;
+      ev[k] = i < nloc * kNQ * kNQ ? a.E[e0 * (kNQ * kNQ) + i] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kAIt; ++k) {
+      const int i = tid + k * kThreads;
+      av[k] = i < nloc * 3 * kNQ * kNQ ? a.star[e0 * (3 * kNQ * kNQ) + i] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kKIt; ++k) {
+      const int i = tid + k * kThreads;
+      kv[k] = i < nnz ? ktab[i] : R(0);
+    }
+    unsigned bad = 0;  // input conditions the elimination without pivoting cannot take
+#pragma unroll
+    for (int k = 0; k < kEIt; ++k) {
+      const int i = tid + k * kThreads;
+      const int r = (i / kNQ) % kNQ, c = i % kNQ;
+      const double v = a.dt * ev[k];
+      if (c < r && v != 0.0) bad |= kInputNotUpper;
+      if (c == r && v >= 0.5) bad |= kInputSingular;
+      if (i < kE * kNQ * kNQ) (&sh.u.s.G[0][0][0])[i] = c >= r ? v : 0.0;
+    }
+    if (bad && a.status) atomicOr(a.status, bad);
+#pragma unroll
+    for (int k = 0; k < kAIt; ++k) {
+      const int i = tid + k * kThreads;
+      if (i < 3 * kE * kNQ * kNQ) (&sh.u.s.A[0][0][0][0])[i] = -(a.dt * av[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kKIt; ++k) {
+      const int i = tid + k * kThreads;
+      if (i < kTab) sh.khat[i] = kv[k];
+    }
+  }
+  for (int i = tid; i < C::kRows; i += kThreads) sh.pos[i] = kSolveLayout<N>.pos[i];
+  if (u == 0) sh.row[pos] = row;
+  if (tid == 0) {
+    sh.flags = 0;
+    sh.maxlevel = 0;
+  }
+  const bool valid = row >= 0;  // the lane holds a column (of an element past the end, if not active)
+  const int es = valid ? row / kNQ : 0, p = valid ? row - es * kNQ : 0;
+  const bool active = valid && es < nloc;
+  const int arow = active ? row : 0;
+  // uniform bases and 32-bit lane offsets of this lane's row
+  const char* const Q0b = reinterpret_cast<const char*>(a.Q0 + e0 * (kNQ * B));
+  char* const Qb = reinterpret_cast<char*>(a.Q + e0 * (kNQ * B * T));
+  char* const Ib = reinterpret_cast<char*>(a.Qint ? a.Qint + e0 * (kNQ * B) : nullptr);
+  const char* const Rb = reinterpret_cast<const char*>(rin ? rin + e0 * (kNQ * B * T) : nullptr);
+  const unsigned q0off = static_cast<unsigned>(arow * (B * 8));
+  const unsigned ioff = q0off + 8 * u;
+  const unsigned qoff = static_cast<unsigned>(arow * (B * T * 8) + 16 * u);
+  const unsigned roff = static_cast<unsigned>(arow * (B * T * 4) + 4 * u);
+  auto load_q0 = [&](int m) __attribute__((always_inline)) {
+    return *reinterpret_cast<const double*>(Q0b + q0off + m * 8);
+  };
+  auto load_r = [&](int m) __attribute__((always_inline)) {
+    return *reinterpret_cast<const float*>(Rb + roff + m * (T * 4));
+  };
+  __syncthreads();
+
+  // Q0 of the top block: each group its own row, to LDS below
+  constexpr int kQt = Mode == kInit ? (DN + T - 1) / T : 0;
+  double qt[kQt > 0 ? kQt : 1];
+#pragma unroll
+  for (int k = 0; k < kQt; ++k)
+    qt[k] = k * T + u < DN ? *reinterpret_cast<const double*>(Q0b + ioff + (LN + k * T) * 8) : 0.0;
+  // G coupling of this lane's quantity (the first non-zero right of the
+  // diagonal and their count), and whether that partner couples further
+  int gcount = 0, gp = p;
+  double gcoef = 0.0;
+#pragma unroll
+  for (int q = 1; q < kNQ; ++q) {
+    const double gq = sh.u.s.G[es][p][q];
+    if (valid && q > p && gq != 0.0) {
+      if (gcount == 0) {
+        gcoef = gq;
+        gp = q;
+      }
+      ++gcount;
+    }
+  }
+  bool partner_coupled = false;
+#pragma unroll
+  for (int q = 1; q < kNQ; ++q) partner_coupled = partner_coupled || (q > gp && sh.u.s.G[es][gp][q] != 0.0);
+  const int ppos = gcount ? sh.pos[es * kNQ + gp] : pos;
+  // Row u of (Z - E*_pp I)^-1: two entries of Z^-1 without a diagonal source;
+  // otherwise a dense row from an elimination, done only by waves holding
+  // such a lane.  xc = row . S^-1 w.
+  const double z = valid ? sh.u.s.G[es][p][p] : 0.0;
+  const bool wave_stiff = __builtin_amdgcn_ballot_w64(z != 0.0) != 0;
+  const bool wave_coupled = __builtin_amdgcn_ballot_w64(gcount != 0) != 0;
+  const bool wave_dense = wave_stiff || wave_coupled;
+  const int zc0 = ZS::col[2 * u], zc1 = ZS::col[2 * u + 1];
+  double zv0 = ZS::val[2 * u], zv1 = ZS::val[2 * u + 1];
+  double xc = fma(zv0, sinv_w(zc0), zv1 * sinv_w(zc1)), dc = 0.0;
+  {
+    double r[T];
+#pragma unroll
+    for (int v = 0; v < T; ++v) r[v] = (zc0 == v ? zv0 : 0.0) + (zc1 == v ? zv1 : 0.0);
+    if (wave_stiff) {
+      double e_u[T], zs[T];
+#pragma unroll
+      for (int v = 0; v < T; ++v) e_u[v] = (v == u) ? 1.0 : 0.0;
+      zt_solve<T>(z, e_u, zs);
+      if (z != 0.0) {
+        xc = 0.0;
+#pragma unroll
+        for (int v = 0; v < T; ++v) {
+          r[v] = zs[v];
+          xc = fma(zs[v], sinv_w(v), xc);
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < T; ++v) sh.rows[tid][v] = r[v];
+  }
+  // sparse row p of the three star matrices: the columns with a non-zero in
+  // any direction, in ascending order
+  __builtin_amdgcn_sched_barrier(0);  // the elimination's registers are free before these are taken
+  unsigned mask = 0;
+#pragma unroll
+  for (int q = 0; q < kNQ; ++q) {
+    const double v0 = sh.u.s.A[es][0][p][q], v1 = sh.u.s.A[es][1][p][q], v2 = sh.u.s.A[es][2][p][q];
+    if (valid && (v0 != 0.0 || v1 != 0.0 || v2 != 0.0)) mask |= 1u << q;
+  }
+  const int npop = __builtin_popcount(mask);
+  // columns the wave's longest row needs (wave-uniform: 2, 4 or 6)
+  const int ns = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(npop > 4)   ? 6
+                                                : __builtin_amdgcn_ballot_w64(npop > 2) ? 4
+                                                                                        : 2);
+  R sa0[kStarNnz], sa1[kStarNnz], sa2[kStarNnz];
+  LdsR* sp[kStarNnz];
+  LdsR* const x0 = (LdsR*)&sh.u.x[0];
+#pragma unroll
+  for (int k = 0; k < kStarNnz; ++k) {
+    const bool live = mask != 0;
+    const int q = live ? __builtin_ctz(mask) : p;
+    mask &= mask - 1;
+    const double v0 = sh.u.s.A[es][0][p][q], v1 = sh.u.s.A[es][1][p][q], v2 = sh.u.s.A[es][2][p][q];
+    sa0[k] = live ? static_cast<R>(v0) : R(0);
+    sa1[k] = live ? static_cast<R>(v1) : R(0);
+    sa2[k] = live ? static_cast<R>(v2) : R(0);
+    sp[k] = x0 + (live ? sh.pos[es * kNQ + q] : pos) * S + u;
+  }
+  {
+    const bool other_wave = ppos / GW != pos / GW;
+    const unsigned f = (active && npop > kStarNnz ? kDenseStar : 0u) |
+                       (active && (gcount > 1 || (gcount == 1 && (partner_coupled || other_wave || z != 0.0))) ? kGeneralE : 0u);
+    if (f) atomicOr(&sh.flags, f);
+  }
+  __syncthreads();
+  const unsigned flags = __builtin_amdgcn_readfirstlane(sh.flags);
+  const bool dense_star = (flags & kDenseStar) != 0, closure = (flags & kGeneralE) == 0;
+  if (!closure) {
+    // dependency levels of a general upper-triangular E (level = longest
+    // coupling chain below a quantity), one thread per element
+    if (tid < nloc) {
+      int lev[kNQ];
+      int mx = 0;
+#pragma unroll
+      for (int o = kNQ - 1; o >= 0; --o) {
+        int l = 0;
+#pragma unroll
+        for (int q = o + 1; q < kNQ; ++q)
+          if (sh.u.s.G[tid][o][q] != 0.0 && lev[q] + 1 > l) l = lev[q] + 1;
+        lev[o] = l;
+        sh.level[tid * kNQ + o] = l;
+        mx = l > mx ? l : mx;
+      }
+      atomicMax(&sh.maxlevel, mx);
+    }
+    __syncthreads();
+  } else if (wave_dense) {
+    // closure row of a coupled lane, X_o = Zinv_o (b_o + g X_p) = zr . b_o + dr . b_p:
+    //   dr[w] = g sum_v (row u of Zinv_o)[v] Zinv_p[v][w],
+    // the rows Zinv_p[v] being those of the partner's lanes of this wave.
+    // After it a lane's dense row is: stiff lanes their row of Zinv (on their
+    // own b), coupled lanes dr (on the partner's b), the others zero.
+    double r[T];
+#pragma unroll
+    for (int w = 0; w < T; ++w) r[w] = 0.0;
+    if (gcount == 1) {
+      const int plane = wave * 64 + (ppos - wave * GW) * T;
+#pragma unroll
+      for (int w = 0; w < T; ++w) {
+        r[w] = gcoef * fma(zv0, sh.rows[plane + zc0][w], zv1 * sh.rows[plane + zc1][w]);
+        dc = fma(r[w], sinv_w(w), dc);
+      }
+    }
+    wave_fence();
+    if (z == 0.0) {
+#pragma unroll
+      for (int w = 0; w < T; ++w) sh.rows[tid][w] = r[w];
+    } else {
+      zv0 = zv1 = 0.0;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kQt; ++k)
+    if (k * T + u < DN) sh.q0[pos * DN + k * T + u] = qt[k];
+  wave_fence();
+
+  // rows of b below the top block, loaded after the setup (its elimination
+  // needs the registers); float64 Q0 rows are scaled when they have arrived
+  constexpr bool kScaleLate = Mode == kInit && std::is_same_v<R, double>;
+  R b[C::LR];
+  const double w_u = sinv_w(u);
+#pragma unroll
+  for (int n = 0; n < LN; ++n) {
+    if constexpr (kScaleLate) b[n] = load_q0(n);
+    else if constexpr (Mode == kInit) b[n] = static_cast<R>(load_q0(n) * w_u);
+    else b[n] = static_cast<R>(load_r(n));
+  }
+  LdsR* const xg = x0 + pos * S;            // the group's block
+  LdsR* const xs = x0 + ppos * S;           // what the dense row applies to
+  LdsD* const qg = (LdsD*)&sh.q0[0] + pos * DN;
+  LdsD* const qp = (LdsD*)&sh.q0[0] + ppos * DN;
+
+  // residual rows of a top-block chunk (kCorrect), loaded one chunk ahead
+  constexpr int kTop0 = chunk_size(N, C::kChunk, 0);
+  R rtop[Mode == kCorrect ? kTop0 : 1];
+  if constexpr (Mode == kCorrect) {
+#pragma unroll
+    for (int k = 0; k < kTop0; ++k) rtop[k] = static_cast<R>(load_r(LN + k));
+  }
+
+  static_for<0, N + 1>([&](auto gi) __attribute__((always_inline)) {
+    constexpr int g = N - decltype(gi)::value;
+    static_for<0, nchunks(g, C::kChunk)>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int cidx = decltype(ci)::value;
+      constexpr int m0 = chunk_start(g, C::kChunk, cidx), c = chunk_size(g, C::kChunk, cidx);
+      constexpr int xb = (chunk_index(N, g, cidx, C::kChunk) & 1) * C::kBuf;
+      constexpr int np = c * T / 2, nst = (np + T - 1) / T, nin = (c + T - 1) / T;
+      constexpr bool odd = (c * T) % 2 != 0, green = g > 0;
+      // the lane's addresses, formed anew for each chunk (an opaque copy of
+      // u): held over the multiply-adds they would cost a wave per SIMD
+      int uc = u;
+      asm volatile("" : "+v"(uc));
+      LdsR* const xl = xg + uc;               // the lane's column
+      LdsR* const xo = xg + 2 * uc;           // its output pairs
+      LdsR* const xi = xg + uc * T;           // its Qint values
+      LdsR* const kl = (LdsR*)&sh.khat[0] + (lane & 15);
+      // kCorrect: the previous outputs, in flight until they are added to
+      pair_t qprev[Mode == kCorrect && nst > 0 ? nst : 1];
+      double qlast = 0.0, iprev[Mode == kCorrect ? nin : 1];
+      if constexpr (Mode == kCorrect) {
+#pragma unroll
+        for (int j = 0; j < nst; ++j)
+          if ((j + 1) * T <= np || j * T + u < np)
+            qprev[j] = *reinterpret_cast<const pair_t*>(Qb + qoff + (m0 * T + j * 2 * T) * 8);
+        if constexpr (odd) {
+          if (u == 0) qlast = *reinterpret_cast<const double*>(Qb + qoff + (m0 * T + c * T - 1) * 8);
+        }
+        if (a.Qint) {
+#pragma unroll
+          for (int k = 0; k < nin; ++k)
+            if ((k + 1) * T <= c || k * T + u < c)
+              iprev[k] = *reinterpret_cast<const double*>(Ib + ioff + (m0 + k * T) * 8);
+        }
+      }
+      // ---- X of the chunk: dark-blue blocks and G coupling (float64)
+      if (Mode == kInit && g == N && closure) {
+        if (wave_coupled) {
+#pragma unroll
+          for (int k = 0; k < c; ++k)
+            xl[xb + k * T] = static_cast<R>(fma(xc, qg[m0 - LN + k], dc * qp[m0 - LN + k]));
+        } else {
+#pragma unroll
+          for (int k = 0; k < c; ++k) xl[xb + k * T] = static_cast<R>(xc * qg[m0 - LN + k]);
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < c; ++k) {
+          if constexpr (g < N) xl[xb + k * T] = b[m0 + k];
+          else if constexpr (Mode == kInit) xl[xb + k * T] = static_cast<R>(qg[m0 - LN + k] * sinv_w(uc));
+          else xl[xb + k * T] = rtop[k];
+        }
+        wave_fence();
+        if (closure) {
+          // columns of the two entries of a row of Z^-1: max(u - 1, 0), min(u + 1, N)
+          LdsR* const xz0 = xg + (uc > 0 ? uc - 1 : 0);
+          LdsR* const xz1 = xg + (uc < N ? uc + 1 : N);
+          double x[c];
+#pragma unroll
+          for (int k = 0; k < c; ++k)
+            x[k] = fma(zv0, static_cast<double>(xz0[xb + k * T]), zv1 * static_cast<double>(xz1[xb + k * T]));
+          if (wave_dense) {
+            double r[T];
+#pragma unroll
+            for (int v = 0; v < T; ++v) r[v] = sh.rows[tid][v];
+#pragma unroll
+            for (int k = 0; k < c; ++k)
+#pragma unroll
+              for (int v = 0; v < T; ++v) x[k] = fma(r[v], static_cast<double>(xs[xb + k * T + v]), x[k]);
+          }
+          wave_fence();
+#pragma unroll
+          for (int k = 0; k < c; ++k) xl[xb + k * T] = static_cast<R>(x[k]);
+        } else {
+          // level by level, in place: a lane reads its group's b and the X of
+          // the levels below, then the group's lanes overwrite b with X
+          const int row = sh.row[pos], es = row / kNQ, p = row - es * kNQ;
+          const int mylevel = active ? sh.level[row] : 0, maxlevel = __builtin_amdgcn_readfirstlane(sh.maxlevel);
+#pragma unroll 1
+          for (int lv = 0; lv <= maxlevel; ++lv) {
+            if (lv > 0) __syncthreads();
+            if (mylevel == lv) {
+#pragma unroll 1
+              for (int k = 0; k < c; ++k) {
+                double x = 0.0;
+#pragma unroll 1
+                for (int v = 0; v < T; ++v) {
+                  double acc = static_cast<double>(xg[xb + k * T + v]);
+                  if (lv > 0) {
+#pragma unroll 1
+                    for (int q = p + 1; q < kNQ; ++q) {
+                      const double gq = a.dt * a.E[((e0 + es) * kNQ + p) * kNQ + q];
+                      if (gq != 0.0) acc = fma(gq, static_cast<double>(x0[sh.pos[es * kNQ + q] * S + xb + k * T + v]), acc);
+                    }
+                  }
+                  x = fma(sh.rows[tid][v], acc, x);
+                }
+                wave_fence();
+                xl[xb + k * T] = static_cast<R>(x);
+              }
+            }
+          }
+        }
+      }
+      if constexpr (Mode == kCorrect && g == N && cidx + 1 < nchunks(N, C::kChunk)) {
+        constexpr int cn = chunk_size(N, C::kChunk, cidx + 1), mn = chunk_start(N, C::kChunk, cidx + 1);
+#pragma unroll
+        for (int k = 0; k < cn; ++k) rtop[k] = static_cast<R>(load_r(mn + k));
+      }
+      if constexpr (kScaleLate && green && g == N && cidx == 0) {
+        // b[p, n, u] = Q0[p, n] (S^-1 w)_u (eq:b_pmu)
+#pragma unroll
+        for (int n = 0; n < LN; ++n) b[n] *= w_u;
+      }
+      wave_fence();
+      if constexpr (green) __syncthreads();
+      // ---- outputs of the chunk from the group's own block: Q <- X or
+      // Q <- Q + X, and Qint = dt X[:, :, 0]; issued after the green update
+      // (the block lives until the chunk after the next)
+      auto store_outputs = [&]() __attribute__((always_inline)) {
+        pair_t v[nst > 0 ? nst : 1];
+        double last = 0.0, iv[nin];
+#pragma unroll
+        for (int j = 0; j < nst; ++j) {
+          v[j].x = static_cast<double>(xo[xb + j * 2 * T]);
+          v[j].y = static_cast<double>(xo[xb + j * 2 * T + 1]);
+        }
+        if constexpr (odd) last = static_cast<double>(xg[xb + c * T - 1]);
+#pragma unroll
+        for (int k = 0; k < nin; ++k) iv[k] = a.dt * static_cast<double>(xi[xb + k * T * T]);
+        if constexpr (Mode == kCorrect) {
+#pragma unroll
+          for (int j = 0; j < nst; ++j) v[j] += qprev[j];
+          last += qlast;
+#pragma unroll
+          for (int k = 0; k < nin; ++k) iv[k] += iprev[k];
+        }
+        if (active) {
+#pragma unroll
+          for (int j = 0; j < nst; ++j)
+            if ((j + 1) * T <= np || j * T + u < np)
+              *reinterpret_cast<pair_t*>(Qb + qoff + (m0 * T + j * 2 * T) * 8) = v[j];
+          if constexpr (odd) {
+            if (u == 0) *reinterpret_cast<double*>(Qb + qoff + (m0 * T + c * T - 1) * 8) = last;
+          }
+          if (a.Qint) {
+#pragma unroll
+            for (int k = 0; k < nin; ++k)
+              if ((k + 1) * T <= c || k * T + u < c)
+                *reinterpret_cast<double*>(Ib + ioff + (m0 + k * T) * 8) = iv[k];
+          }
+        }
+      };
+      // ---- green blocks: y_j = (A^{j*} X)_p of each mode, then the Khat
+      // column on the lane's rows.  The X reads of a mode are issued before
+      // the multiply-adds of the mode before it.
+      if constexpr (green) {
+        R xq[kStarNnz], y0 = R(0), y1 = R(0), y2 = R(0);
+        auto read_x = [&](auto k) __attribute__((always_inline)) {
+          constexpr int off = xb + decltype(k)::value * T;
+          xq[0] = sp[0][off];
+          xq[1] = sp[1][off];
+          if (ns > 2) {
+            asm volatile("");  // keep these branches: the rows are 2, 4 or 6 long for a whole wave
+            xq[2] = sp[2][off];
+            xq[3] = sp[3][off];
+          }
+          if (ns > 4) {
+            asm volatile("");
+            xq[4] = sp[4][off];
+            xq[5] = sp[5][off];
+          }
+        };
+        auto star = [&](auto k) __attribute__((always_inline)) {
+          if (!dense_star) {
+            y0 = sa0[0] * xq[0];
+            y1 = sa1[0] * xq[0];
+            y2 = sa2[0] * xq[0];
+            auto add = [&](int i) __attribute__((always_inline)) {
+              y0 = fma(sa0[i], xq[i], y0);
+              y1 = fma(sa1[i], xq[i], y1);
+              y2 = fma(sa2[i], xq[i], y2);
+            };
+            add(1);
+            if (ns > 2) {
+              asm volatile("");
+              add(2);
+              add(3);
+            }
+            if (ns > 4) {
+              asm volatile("");
+              add(4);
+              add(5);
+            }
+          } else {
+            const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? 0 : row - es * kNQ;
+            const double* st = a.star + (active ? e0 + es : e0) * (3 * kNQ * kNQ) + p * kNQ;
+            y0 = y1 = y2 = R(0);
+#pragma unroll 1
+            for (int q = 0; q < kNQ; ++q) {
+              const R xv = x0[sh.pos[es * kNQ + q] * S + uc + xb + decltype(k)::value * T];
+              y0 = fma(static_cast<R>(-(a.dt * st[q])), xv, y0);
+              y1 = fma(static_cast<R>(-(a.dt * st[kNQ * kNQ + q])), xv, y1);
+              y2 = fma(static_cast<R>(-(a.dt * st[2 * kNQ * kNQ + q])), xv, y2);
+            }
+          }
+        };
+        // groups of 16 coefficients [G0, G1) of this chunk, kAhead in flight
+        constexpr int kAhead = 2;
+        constexpr int first = P::col_start[m0], last = P::col_start[m0 + c - 1] + P::col_count[m0 + c - 1];
+        constexpr int G0 = first / 16, G1 = (last + 15) / 16;
+        R kc[kAhead + 1];
+        read_x(ic<0>{});
+        static_for<0, (kAhead < G1 - G0 ? kAhead : G1 - G0)>([&](auto i) __attribute__((always_inline)) {
+          kc[(G0 + decltype(i)::value) % (kAhead + 1)] = kl[(G0 + decltype(i)::value) * 16];
+        });
+        star(ic<0>{});
+        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
+          constexpr int kk = decltype(k)::value, m = m0 + kk;
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (kk + 1 < c) read_x(ic<kk + 1>{});
+          static_for<0, P::col_count[m]>([&](auto i) __attribute__((always_inline)) {
+            constexpr int e = P::col_start[m] + decltype(i)::value, G = e / 16;
+            if constexpr ((e % 16 == 0 || e == first) && G + kAhead < G1) {
+              __builtin_amdgcn_sched_barrier(0);
+              kc[(G + kAhead) % (kAhead + 1)] = kl[(G + kAhead) * 16];
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            constexpr int j = P::dir[e];
+            fmac_bcast<e % 16>(b[P::row[e]], kc[G % (kAhead + 1)], (j == 0) ? y0 : ((j == 1) ? y1 : y2));
+          });
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (kk + 1 < c) star(ic<kk + 1>{});
+        });
+      }
+      store_outputs();
+    });
+  });
+}
+
+template <int N, typename R, int Mode>
+hipError_t launch_solve(const PredictArgs& a, const float* rin, hipStream_t stream) {
+  using C = SolveCfg<N>;
+  const int64_t groups = (a.n + C::kE - 1) / C::kE;
+  if (groups > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((solve_kernel<N, R, Mode>), dim3(static_cast<unsigned>(groups)), dim3(C::kThreads), 0, stream, a,
+                     rin);
+  return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace stp
