@@ -11,17 +11,15 @@
 // term is the integrated-by-parts flux form of A q_x + B q_y + C q_z, the face
 // term Godunov's upwind flux An^+ q^- + An^- q^+ across each face.
 //
-// One workgroup (4 waves) per element, one kernel per (quantity count,
-// degree).  The own and the four neighbours' Qint and the 12 operators (E
-// and the 11 terms' G, with the terms' signs folded in) are staged in LDS;
-// then, in groups of WN terms, W_m = G_m X_m (nq x B) is formed in LDS on
-// the vector ALU and the products W_m T_m are accumulated on the matrix cores
-// (v_mfma_f64_16x16x4f64): rows = quantities (padded to 16), columns = the
-// element's modes in tiles of 16 (tile t on wave t mod 4), the inner
-// dimension the table's rows in steps of 4.  The accumulators stay in
-// registers over all 11 terms; E Qint is added on the vector ALU before the
-// single read-modify-write of Q.  The tables are read from global memory
-// (they are shared by all elements and stay in the caches).
+// Every term is a product G X T (quantities x quantities, quantities x modes,
+// modes x modes) and both products run on the float64 matrix cores
+// (v_mfma_f64_16x16x4f64), one wave per element and range of output tiles,
+// without LDS and without barriers: W^T = X^T G^T is formed tile by tile (16
+// modes x 16 quantities, 4 instructions), and its accumulator registers are,
+// as they stand, the A operand of W T: register r of lane l holds quantity
+// l % 16 of mode 4 r + l / 16 of the tile, exactly what step r needs.  X^T, G^T
+// and the tables are read straight from memory (Qint and the operators once
+// per element, the tables from the caches, prefetched one term ahead).
 #include "common.hpp"
 
 namespace stp {
@@ -29,217 +27,201 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kCorrThreads = 256;
-constexpr int kCorrWaves = kCorrThreads / 64;
-constexpr int kTerms = 11;
-
-template <int NQ, int N>
-struct CorrCfg {
-  static constexpr int B = n_modes(N);
-  static constexpr int QB = NQ * B;
-  static constexpr int Q2 = NQ * NQ;
-  static constexpr int NT = (B + 15) / 16;                 // column tiles
-  static constexpr int TPW = (NT + kCorrWaves - 1) / kCorrWaves;  // tiles per wave
-  static constexpr int KS = (B + 3) / 4;                   // inner steps of 4
-  static constexpr int WS = 4 * KS + 1;                    // W row stride (odd: no bank conflicts)
-  static constexpr int kW = 16 * WS;                       // one term's W, 16 rows (zero past NQ)
-  static constexpr size_t lds_doubles(int wn) {
-    return static_cast<size_t>(5) * QB + static_cast<size_t>(12) * Q2 + static_cast<size_t>(wn) * kW;
-  }
-  // terms per group: the most that still let three workgroups share a
-  // compute unit's 160 KB of LDS, else two, else one (at N=4 with 13
-  // quantities, 3 workgroups of 4-term groups: 5.6 ms per 163,840 elements,
-  // against 7.0 ms for 2 workgroups of 6-term groups and 8.3-11.3 ms for 4
-  // workgroups of single terms)
-  static constexpr int pick_wn() {
-    constexpr int cand[6] = {11, 6, 4, 3, 2, 1};
-    constexpr size_t limit[3] = {160 * 1024 / 3, 80 * 1024, 160 * 1024};
-    for (int b = 0; b < 3; ++b)
-      for (int i = 0; i < 6; ++i)
-        if (lds_doubles(cand[i]) * 8 <= limit[b]) return cand[i];
-    return 0;
-  }
-  static constexpr int WN = pick_wn();
-  static_assert(WN >= 1, "the corrector tile does not fit LDS");
-  static constexpr size_t kLds = lds_doubles(WN) * 8;
-  // the next term's table entries are loaded while the current term's
-  // matrix-core products run, when the two register sets are small
-  static constexpr bool kPrefetch = TPW * KS <= 24;
-  static constexpr int kBuf = kPrefetch ? 2 : 1;
-  // staging loads per thread: each source's Qint rows, and the 12 operators
-  // (all issued before the first LDS store; issuing the next element's
-  // during the current one measured slower, as its registers cost a
-  // workgroup per compute unit)
-  static constexpr int kXPer = (QB + kCorrThreads - 1) / kCorrThreads;
-  static constexpr int kGPer = (12 * Q2 + kCorrThreads - 1) / kCorrThreads;
-};
-
-// Position (row i, column j) of accumulator entry r of lane l in the 16x16
-// tile of v_mfma_f64_16x16x4f64, whose operands are lane l's A[l % 16][l / 16]
-// and B[l / 16][l % 16]: row l / 16 + 4 r, column l % 16 (unlike the float32
-// 16x16x4 instruction, whose rows are 4 (l / 16) + r; checked on gfx950 with
-// an in-bounds probe of one wave).
-__device__ __forceinline__ void acc_pos(int l, int r, int& i, int& j) {
-  i = l / 16 + 4 * r;
-  j = l % 16;
+__device__ __forceinline__ v4d mfma(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <int NQ, int N>
-__global__ __launch_bounds__(kCorrThreads) void corrector_kernel(CorrectArgs a) {
-  using C = CorrCfg<NQ, N>;
-  constexpr int B = C::B, QB = C::QB, Q2 = C::Q2, WN = C::WN;
-  extern __shared__ double lds[];
-  double* X = lds;                 // [5][NQ][B]: own, neighbours 0..3
-  double* G = X + 5 * QB;          // [12][NQ][NQ]: E, then the 11 terms' operators (signed)
-  double* W = G + 12 * Q2;         // [WN][16][WS]
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+// Operand layout of v_mfma_f64_16x16x4f64 (checked on gfx950 with an in-bounds
+// probe of one wave): lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
+// accumulator register r of lane l is row l / 16 + 4 r, column l % 16.
+//
+// TPW: output tiles (16 modes) per wave; an element takes
+// ceil(NT / TPW) waves.
+template <int NQ, int N, int TPW>
+__global__ __launch_bounds__(256, TPW > 1 ? 2 : 3) void corrector_kernel(CorrectArgs a) {
+  constexpr int B = n_modes(N), QB = NQ * B, Q2 = NQ * NQ;
+  constexpr int NT = (B + 15) / 16, kParts = (NT + TPW - 1) / TPW, QS = (NQ + 3) / 4;
   constexpr size_t BB = static_cast<size_t>(B) * B;
-  const double* Vt = a.tables;                 // [3][B][B]
-  const double* Fl = a.tables + 3 * BB;        // [4][B][B]
-  const double* Fn = a.tables + 7 * BB;        // [4][4][6][B][B]
-  // the padding of W (rows >= NQ, columns >= B) stays zero
-  for (int i = tid; i < WN * C::kW; i += kCorrThreads) W[i] = 0.0;
-  // staging of element e: every load issued before any LDS store
-  double xs[5][C::kXPer], gs[C::kGPer];
-  auto fetch = [&](int64_t e) __attribute__((always_inline)) {
+  const int lane = threadIdx.x % 64, col = lane % 16, kq = lane / 16;
+  const int64_t unit =
+      static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+  const int64_t e = unit / kParts;
+  if (e >= a.n) return;
+  const int c0 = static_cast<int>(unit % kParts) * TPW;  // first output tile of this wave
+  const double* const Vt = a.tables;           // [3][B][B]
+  const double* const Fl = a.tables + 3 * BB;  // [4][B][B]
+  const double* const Fn = a.tables + 7 * BB;  // [4][4][6][B][B]
+
+  // lane offsets of the output columns: tile c0 + c, clamped to the table
+  // (columns past B - 1 are computed from the last one and not stored)
+  int coff[TPW];
 #pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      const int64_t src = s == 0 ? e : a.neighbor[e * 4 + (s - 1)];
+  for (int c = 0; c < TPW; ++c) {
+    const int j = 16 * (c0 + c) + col;
+    coff[c] = j < B ? j : B - 1;
+  }
+  // X^T tile t of a Qint block: mode 16 t + col, quantities 4 s + kq (zero past the end)
+  auto load_x = [&](const double* X, int t, double (&x)[QS]) __attribute__((always_inline)) {
+    const int l = 16 * t + col;
 #pragma unroll
-      for (int k = 0; k < C::kXPer; ++k) {
-        const int i = tid + k * kCorrThreads;
-        xs[s][k] = i < QB ? a.Qint[src * QB + i] : 0.0;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < C::kGPer; ++k) {
-      const int i = tid + k * kCorrThreads;
-      const int m = i / Q2, j = i % Q2;
-      const double* src = m == 0 ? a.E + e * Q2
-                        : m <= 3 ? a.star + (e * 3 + (m - 1)) * Q2
-                        : m <= 7 ? a.Gp + (e * 4 + (m - 4)) * Q2
-                                 : a.Gm + (e * 4 + (m - 8)) * Q2;
-      gs[k] = i < 12 * Q2 ? src[j] : 0.0;
-    }
-  };
-  auto stash = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < 5; ++s)
-#pragma unroll
-      for (int k = 0; k < C::kXPer; ++k) {
-        const int i = tid + k * kCorrThreads;
-        if (i < QB) X[s * QB + i] = xs[s][k];
-      }
-#pragma unroll
-    for (int k = 0; k < C::kGPer; ++k) {
-      const int i = tid + k * kCorrThreads;
-      if (i < 12 * Q2) G[i] = i / Q2 >= 4 ? -gs[k] : gs[k];  // face terms enter with a minus sign
+    for (int s = 0; s < QS; ++s) {
+      const int q = 4 * s + kq;
+      x[s] = (l < B && q < NQ) ? X[q * B + l] : 0.0;
     }
   };
-  for (int64_t e = blockIdx.x; e < a.n; e += gridDim.x) {
-    fetch(e);
-    __syncthreads();  // the previous element's LDS reads are done
-    stash();
-    int code[4];
+  // G^T: quantities 4 s + kq (rows) to quantity col (zero past the end)
+  auto load_g = [&](const double* G, double sign, double (&g)[QS]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f) code[f] = a.nb_code[e * 4 + f];
-    // this wave's B operands (table entries) of term m: tile t = wave + 4 tt,
-    // inner step s; zero outside the B x B table
-    auto load_b = [&](int m, double (&bv)[C::TPW][C::KS]) __attribute__((always_inline)) {
-      const double* T = m < 3 ? Vt + m * BB
-                       : m < 7 ? Fl + (m - 3) * BB
-                               : Fn + (static_cast<size_t>(m - 7) * 24 + code[m - 7]) * BB;
-#pragma unroll
-      for (int tt = 0; tt < C::TPW; ++tt) {
-        const int col = 16 * (wave + kCorrWaves * tt) + lane % 16;
-#pragma unroll
-        for (int s = 0; s < C::KS; ++s) {
-          const int row = 4 * s + lane / 16;
-          bv[tt][s] = (row < B && col < B) ? T[row * B + col] : 0.0;
-        }
-      }
-    };
-    v4d acc[C::TPW];
-#pragma unroll
-    for (int tt = 0; tt < C::TPW; ++tt) acc[tt] = v4d{0.0, 0.0, 0.0, 0.0};
-    double bv[C::kBuf][C::TPW][C::KS];
-    if constexpr (C::kPrefetch) load_b(0, bv[1]);  // overlaps the first W phase
-    for (int m0 = 0; m0 < kTerms; m0 += WN) {
-      const int mcount = kTerms - m0 < WN ? kTerms - m0 : WN;
-      __syncthreads();  // staging done (first group) / previous group's W reads done
-      // W_m = G_m X_m for the group's terms (vector ALU)
-      for (int i = tid; i < mcount * QB; i += kCorrThreads) {
-        const int mm = i / QB, r = i % QB, p = r / B, l = r % B;
-        const int m = m0 + mm;
-        const double* Xm = X + (m < 7 ? 0 : (m - 6) * QB);
-        const double* Gm = G + (1 + m) * Q2 + p * NQ;
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) s = fma(Gm[q], Xm[q * B + l], s);
-        W[mm * C::kW + p * C::WS + l] = s;
-      }
-      __syncthreads();
-      // accumulate W_m T_m on the matrix cores: wave w owns column tiles
-      // w, w + 4, ... (waves without a tile skip this, wave-uniformly)
-      if (wave < C::NT) {
-        for (int mm = 0; mm < mcount; ++mm) {
-          const int m = m0 + mm;
-          if constexpr (C::kPrefetch) {
-#pragma unroll
-            for (int tt = 0; tt < C::TPW; ++tt)
-#pragma unroll
-              for (int s = 0; s < C::KS; ++s) bv[0][tt][s] = bv[1][tt][s];
-            if (m + 1 < kTerms) load_b(m + 1, bv[1]);
-          } else {
-            load_b(m, bv[0]);
-          }
-          const double* Wm = W + mm * C::kW + (lane % 16) * C::WS + lane / 16;
-#pragma unroll
-          for (int s = 0; s < C::KS; ++s) {
-            const double av = Wm[4 * s];
-#pragma unroll
-            for (int tt = 0; tt < C::TPW; ++tt)
-              if (wave + kCorrWaves * tt < C::NT)  // wave-uniform
-                acc[tt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[0][tt][s], acc[tt], 0, 0, 0);
-          }
-        }
-      }
+    for (int s = 0; s < QS; ++s) {
+      const int q = 4 * s + kq;
+      g[s] = (col < NQ && q < NQ) ? sign * G[col * NQ + q] : 0.0;
     }
-    // + E Qint, then Q += the accumulated update
+  };
+  // the four table rows of each inner step of tile t (clamped: W is zero there)
+  auto load_t = [&](const double* T, int t, double (&b)[4][TPW]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int tt = 0; tt < C::TPW; ++tt) {
-      const int t = wave + kCorrWaves * tt;
-      if (t < C::NT) {
+    for (int r = 0; r < 4; ++r) {
+      const int l = 16 * t + 4 * r + kq;
+      const double* row = T + (l < B ? l : B - 1) * B;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int i, j;
-          acc_pos(lane, r, i, j);
-          j += 16 * t;
-          if (i < NQ && j < B) {
-            double v = acc[tt][r];
+      for (int c = 0; c < TPW; ++c) b[r][c] = row[coff[c]];
+    }
+  };
+  v4d acc[TPW];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) v = fma(G[i * NQ + q], X[q * B + j], v);
-            a.Q[e * QB + i * B + j] += v;
-          }
-        }
+  for (int c = 0; c < TPW; ++c) acc[c] = v4d{0.0, 0.0, 0.0, 0.0};
+  // acc += (G X)_tile t . T rows; upper: the table has zeros on and below the
+  // diagonal blocks (V: degree l < degree k), so tiles left of t add nothing
+  auto term = [&](const double (&x)[QS], const double (&g)[QS], const double (&b)[4][TPW], int t,
+                  bool upper) __attribute__((always_inline)) {
+    v4d w = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < QS; ++s) w = mfma(x[s], g[s], w);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (16 * t + 4 * r < B) {
+#pragma unroll
+        for (int c = 0; c < TPW; ++c)
+          if (!upper || c0 + c >= t) acc[c] = mfma(w[r], b[r][c], acc[c]);
       }
+  };
+
+  // ---- own block: E, the three volume terms and the four own-face terms
+  const double* const Xo = a.Qint + e * QB;
+  {
+    double g[7][QS];
+#pragma unroll
+    for (int m = 0; m < 7; ++m) load_g(m < 3 ? a.star + (e * 3 + m) * Q2 : a.Gp + (e * 4 + (m - 3)) * Q2, m < 3 ? 1.0 : -1.0, g[m]);
+    double x[QS], b[2][4][TPW];
+    load_x(Xo, 0, x);
+    load_t(Vt, 0, b[0]);
+#pragma unroll 1
+    for (int t = 0; t < NT; ++t) {
+      double xn[QS];
+      load_x(Xo, t + 1 < NT ? t + 1 : t, xn);
+#pragma unroll
+      for (int m = 0; m < 7; ++m) {
+        // the next term's rows in flight during this one's products
+        if (m < 6) load_t(m + 1 < 3 ? Vt + (m + 1) * BB : Fl + (m - 2) * BB, t, b[(m + 1) % 2]);
+        else load_t(Vt, t + 1 < NT ? t + 1 : t, b[(m + 1) % 2]);
+        term(x, g[m], b[m % 2], t, m < 3);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < TPW; ++c) b[0][i][c] = b[1][i][c];
+#pragma unroll
+      for (int s = 0; s < QS; ++s) x[s] = xn[s];
+    }
+  }
+  // ---- neighbours
+#pragma unroll 1
+  for (int f = 0; f < 4; ++f) {
+    const int nb = __builtin_amdgcn_readfirstlane(a.neighbor[e * 4 + f]);
+    const int code = __builtin_amdgcn_readfirstlane(a.nb_code[e * 4 + f]);
+    const double* const X = a.Qint + static_cast<int64_t>(nb) * QB;
+    const double* const T = Fn + (static_cast<size_t>(f) * 24 + code) * BB;
+    double g[QS], x[QS], b[4][TPW];
+    load_g(a.Gm + (e * 4 + f) * Q2, -1.0, g);
+    load_x(X, 0, x);
+    load_t(T, 0, b);
+#pragma unroll 1
+    for (int t = 0; t < NT; ++t) {
+      double xn[QS], bn[4][TPW];
+      const int tn = t + 1 < NT ? t + 1 : t;
+      load_x(X, tn, xn);
+      load_t(T, tn, bn);
+      term(x, g, b, t, false);
+#pragma unroll
+      for (int s = 0; s < QS; ++s) x[s] = xn[s];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < TPW; ++c) b[r][c] = bn[r][c];
+    }
+  }
+  // ---- + E Qint (A operand: rows of E, B operand: rows of Qint), then Q += the update
+  double ge[QS];
+  {
+    const double* const E = a.E + e * Q2;
+#pragma unroll
+    for (int s = 0; s < QS; ++s) {
+      const int q = 4 * s + kq;
+      ge[s] = (col < NQ && q < NQ) ? E[col * NQ + q] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < TPW; ++c) {
+    const int j = 16 * (c0 + c) + col;
+    double x[QS];
+#pragma unroll
+    for (int s = 0; s < QS; ++s) {
+      const int q = 4 * s + kq;
+      x[s] = (j < B && q < NQ) ? Xo[q * B + j] : 0.0;
+    }
+#pragma unroll
+    for (int s = 0; s < QS; ++s) acc[c] = mfma(ge[s], x[s], acc[c]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = kq + 4 * r;
+      if (i < NQ && j < B) a.Q[e * QB + i * B + j] += acc[c][r];
     }
   }
 }
 
+template <int NQ, int N, int TPW>
+hipError_t launch_tiles(const CorrectArgs& a, hipStream_t stream) {
+  constexpr int NT = (n_modes(N) + 15) / 16, kParts = (NT + TPW - 1) / TPW;
+  const int64_t blocks = (a.n * kParts + 3) / 4;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((corrector_kernel<NQ, N, TPW>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+// Output tiles per wave.  Fewer tiles per wave form W more often (4
+// instructions per tile of W against 4 per output tile of it), more of them
+// leave the chip idle while there are fewer waves than SIMDs (1,024).
+// Measured, microseconds (13 quantities):
+//   N = 6, 5,000 elements: 6 tiles 436, 3 tiles 418, 2 tiles 454;
+//          1,080: 167 / 134 / 132;  320: 88 / 56 / 50
+//   N = 7, 8,640 elements: 8 tiles 1,266, 4 tiles 1,107, 3 tiles 1,334
+//   N = 4, 20,480 elements: 3 tiles 495, 2 tiles 646, 1 tile 692;  320: 34 / 29 / 24
+// so degrees of four tiles and more take half of an element per wave (also
+// the registers of two waves per SIMD), the others a whole element, and below
+// one element per SIMD the tiles are spread further.
 template <int NQ, int N>
 hipError_t launch_one(const CorrectArgs& a, hipStream_t stream) {
-  using C = CorrCfg<NQ, N>;
-  const int64_t blocks64 = a.n < 65536 ? a.n : 65536;
-  if (C::kLds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(corrector_kernel<NQ, N>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(C::kLds));
-    if (e != hipSuccess) return e;
+  constexpr int NT = (n_modes(N) + 15) / 16;
+  const bool few = a.n <= 1024;
+  if constexpr (NT >= 4) {
+    if (few) return launch_tiles<NQ, N, (NT + 2) / 3>(a, stream);
+    return launch_tiles<NQ, N, (NT + 1) / 2>(a, stream);
+  } else {
+    if constexpr (NT >= 2) {
+      if (few) return launch_tiles<NQ, N, 1>(a, stream);
+    }
+    return launch_tiles<NQ, N, NT>(a, stream);
   }
-  hipLaunchKernelGGL((corrector_kernel<NQ, N>), dim3(static_cast<unsigned>(blocks64)), dim3(kCorrThreads), C::kLds,
-                     stream, a);
-  return hipGetLastError();
 }
 
 template <int NQ>
