@@ -1,7 +1,7 @@
 // Register-resident kernels for Algorithm 3 of Wolf et al. (arXiv 2108.10565,
 // section "Block-wise back-substitution"), one object per quantity count and
-// degree N = STP_DEGREE: the solve (solve_kernel.hpp), the float32 chain on
-// the matrix cores, and the float64 residual of the mixed-precision path.
+// degree N = STP_DEGREE: the solve and the residual (solve_kernel.hpp), and
+// the float32 chain on the matrix cores.
 //
 // Shared structure.  One lane per column (element e, quantity p, time mode u)
 // of the element's right-hand side b_pmu (eq:b_pmu), which keeps b[m] for all
@@ -52,7 +52,7 @@ namespace {
 constexpr int kNQ = STP_NQ;
 static_assert(supported_nq(kNQ), "quantity count without kernels");
 
-// Tile shape of this degree: threads per workgroup (upper bound; rounded to
+// Tile shape of the matrix-core chain: threads per workgroup (upper bound; rounded to
 // whole elements and waves) and modes per chunk (degree blocks are split
 // evenly).  Both come from the build, which takes them from the table the
 // autotuner writes after timing every candidate shape on the device.
@@ -72,7 +72,6 @@ constexpr int kStarNnz = 6;
 
 template <int I>
 using ic = std::integral_constant<int, I>;
-using ConstUint = __attribute__((address_space(4))) const unsigned;
 
 template <int Begin, class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -236,124 +235,6 @@ __device__ __forceinline__ const R* khat_sparse() {
   }
 }
 
-// Register pinning: an empty asm statement that reads (or reads and writes)
-// a register value.  Volatile asm statements keep their program order, so
-// these fix where a value must be complete and stop the compiler from
-// sinking pure arithmetic or hoisting loads across them.
-template <typename T>
-__device__ __forceinline__ void pin_v(T& x) { asm volatile("" : "+v"(x)); }
-template <typename T>
-__device__ __forceinline__ void use_s(T x) { asm volatile("" ::"s"(x)); }
-
-// Coefficients per scalar load: one s_load_dwordx16 (64 bytes).
-template <typename R>
-constexpr int kGroup = 64 / static_cast<int>(sizeof(R));
-
-// Loads the coefficients [g0, g0 + gn) of the usage-ordered Khat table into
-// scalar registers, from an address the compiler cannot see through.
-template <typename R, int g0, int gn>
-__device__ __forceinline__ void load_group(const R* kv, R (&v)[kGroup<R>]) {
-  using CR = __attribute__((address_space(4))) const R;
-  const R* kp = kv + g0;
-  asm volatile("" : "+s"(kp));
-  const CR* kc = (const CR*)kp;
-#pragma unroll
-  for (int i = 0; i < gn; ++i) v[i] = kc[i];
-}
-
-// Brings the Khat coefficients of columns [M0, M0 + CNT) into the scalar
-// data cache: wave w loads one dword of each line w, w + nwaves, ... of the
-// range (64-byte lines, table 64-byte aligned), issuing every load before
-// waiting once, so the line fetches overlap each other and the other waves'
-// work; the per-group loads of the green update then hit the cache.
-template <int N, typename R, int M0, int CNT, int NWAVES>
-__device__ __forceinline__ void prefetch_columns(const R* kv, int wave) {
-  using P = stp_gen::KhatPattern<N>;
-  constexpr int per_line = 64 / static_cast<int>(sizeof(R));
-  constexpr int first = P::col_start[M0];
-  constexpr int last = P::col_start[M0 + CNT - 1] + P::col_count[M0 + CNT - 1];
-  if constexpr (last > first) {
-    constexpr int line0 = first / per_line, line1 = (last + per_line - 1) / per_line;
-    constexpr int per_wave = (line1 - line0 + NWAVES - 1) / NWAVES;
-    const R* kp = kv + (line0 + wave) * per_line;
-    asm volatile("" : "+s"(kp));
-    const ConstUint* kc = (const ConstUint*)kp;
-    const int avail = line1 - line0 - wave;  // lines this wave may touch: k * NWAVES < avail
-    unsigned v[per_wave];
-#pragma unroll
-    for (int k = 0; k < per_wave; ++k) v[k] = (k * NWAVES < avail) ? kc[k * NWAVES * 16] : 0u;
-#pragma unroll
-    for (int k = 0; k < per_wave; ++k) asm volatile("" ::"s"(v[k]));
-  }
-}
-
-// First coefficient group of column M of the usage-ordered Khat table
-// (possibly partial), issued into `grp` without waiting for it.
-template <int N, int M, typename R>
-__device__ __forceinline__ void load_first_group(const R* kv, R (&grp)[kGroup<R>]) {
-  using P = stp_gen::KhatPattern<N>;
-  constexpr int GS = kGroup<R>;
-  constexpr int count = P::col_count[M];
-  if constexpr (count > 0) load_group<R, P::col_start[M], (count < GS ? count : GS)>(kv, grp);
-}
-
-// b[n] -= Khat^j[n, M] y_j for the non-zeros of column M (usage order of the
-// generated pattern: directions, then rows ascending), in groups of
-// kGroup<R> coefficients.  `cur` arrives holding the column's first group
-// (issued earlier by load_first_group or by the previous column); each
-// group's fused multiply-adds run while the next group's scalar load is in
-// flight, and the last group issues the first group of column MNext (< 0:
-// none), so that a column starts without waiting for its coefficients.
-template <int N, int M, int MNext, typename R>
-__device__ __forceinline__ void green_column(R (&b)[Cfg<N>::LR], R y0, R y1, R y2, const R* kv, R (&cur)[kGroup<R>]) {
-  using P = stp_gen::KhatPattern<N>;
-  constexpr int GS = kGroup<R>;
-  constexpr int start = P::col_start[M];
-  constexpr int count = P::col_count[M];
-  constexpr int ngroups = (count + GS - 1) / GS;
-  constexpr bool kNext = MNext >= 0 && MNext < Cfg<N>::B;
-  constexpr int next_count = kNext ? P::col_count[kNext ? MNext : 0] : 0;
-  if constexpr (count == 0) {
-    if constexpr (next_count > 0) load_first_group<N, (kNext ? MNext : 0), R>(kv, cur);
-  } else {
-#pragma unroll
-    for (int i = 0; i < (count < GS ? count : GS); ++i) use_s(cur[i]);
-    static_for<0, ngroups>([&](auto G) __attribute__((always_inline)) {
-      constexpr int gi = decltype(G)::value;
-      constexpr int g0 = start + gi * GS;
-      constexpr int gn = (start + count - g0) < GS ? (start + count - g0) : GS;
-      constexpr int g1 = g0 + GS;
-      constexpr int gn1 = (start + count - g1) < GS ? (start + count - g1) : GS;
-      constexpr bool kLast = gi + 1 == ngroups;
-      constexpr int nload = kLast ? (next_count < GS ? next_count : GS) : gn1;
-      R nxt[GS];
-      if constexpr (!kLast) load_group<R, g1, gn1>(kv, nxt);
-      else if constexpr (next_count > 0) load_first_group<N, (kNext ? MNext : 0), R>(kv, nxt);
-      static_for<0, gn>([&](auto I) __attribute__((always_inline)) {
-        constexpr int e = g0 + decltype(I)::value;
-        constexpr int n = P::row[e];
-        constexpr int j = P::dir[e];
-        const R y = (j == 0) ? y0 : ((j == 1) ? y1 : y2);
-        b[n] = fma(-cur[decltype(I)::value], y, b[n]);
-      });
-      static_for<0, gn>([&](auto I) __attribute__((always_inline)) {
-        pin_v(b[P::row[g0 + decltype(I)::value]]);
-      });
-      if constexpr (!kLast) {
-#pragma unroll
-        for (int i = 0; i < nload; ++i) {
-          use_s(nxt[i]);
-          cur[i] = nxt[i];
-        }
-      } else if constexpr (nload > 0) {
-        // the next column's first group: handed over without waiting here
-#pragma unroll
-        for (int i = 0; i < nload; ++i) cur[i] = nxt[i];
-      }
-    });
-  }
-}
-
 // Copies columns [m0 T, m0 T + PER) of the (element, quantity) rows of the
 // group (a [n][kNQ][B T] array in memory) into the chunk buffer `buf` (block
 // layout of Cfg::blk), converted to R.  Every lane issues all its loads
@@ -379,67 +260,13 @@ __device__ __forceinline__ void stage_rows(R* buf, const Src* src, int64_t e0, i
   }
 }
 
-// The two halves of stage_rows, for callers that overlap the loads with
-// other work: the loads of columns [m0 T, m0 T + PER) into registers, then
-// their stores into the chunk buffer.
-template <int N, int PER>
-struct RowStage {
-  using C = Cfg<N>;
-  static constexpr int kIters = (C::kElems * kNQ * PER + C::kThreads - 1) / C::kThreads;
-  double v[kIters];
-  __device__ __forceinline__ void issue(const double* src, int64_t e0, int m0T, int nloc, int tid) {
-    const int limit = nloc * kNQ * PER;
-#pragma unroll
-    for (int k = 0; k < kIters; ++k) {
-      const int i = tid + k * C::kThreads;
-      const int row = i / PER, r = i % PER;
-      v[k] = i < limit ? src[(e0 * kNQ + row) * (C::B * C::T) + m0T + r] : 0.0;
-    }
-  }
-  __device__ __forceinline__ void commit(double* buf, int nloc, int tid) const {
-    const int limit = nloc * kNQ * PER;
-#pragma unroll
-    for (int k = 0; k < kIters; ++k) {
-      const int i = tid + k * C::kThreads;
-      const int row = i / PER, r = i % PER;
-      if (i < limit) buf[C::rowblk(row) + r] = v[k];
-    }
-  }
-};
-
-// Q0 of the CM modes starting at m0 of the group, [element][quantity][mode],
-// in the same two halves.
-template <int N, int CM>
-struct Q0Stage {
-  using C = Cfg<N>;
-  static constexpr int kIters = (C::kElems * kNQ * CM + C::kThreads - 1) / C::kThreads;
-  double v[kIters];
-  __device__ __forceinline__ void issue(const double* Q0, int64_t e0, int m0, int nloc, int tid) {
-#pragma unroll
-    for (int k = 0; k < kIters; ++k) {
-      const int i = tid + k * C::kThreads;
-      v[k] = i < nloc * kNQ * CM ? Q0[(e0 * kNQ + i / CM) * C::B + m0 + i % CM] : 0.0;
-    }
-  }
-  __device__ __forceinline__ void commit(double* buf, int nloc, int tid) const {
-#pragma unroll
-    for (int k = 0; k < kIters; ++k) {
-      const int i = tid + k * C::kThreads;
-      if (i < nloc * kNQ * CM) buf[i] = v[k];
-    }
-  }
-};
-
 // Position of chunk ci of degree block g in the chunk order (blocks from N
-// down, chunks ascending), and the chunk that follows it.
+// down, chunks ascending).
 __host__ __device__ constexpr int chunk_index(int N, int g, int ci, int cmax) {
   int s = 0;
   for (int h = N; h > g; --h) s += nchunks(h, cmax);
   return s + ci;
 }
-__host__ __device__ constexpr int next_block(int g, int ci, int cmax) { return ci + 1 < nchunks(g, cmax) ? g : g - 1; }
-__host__ __device__ constexpr int next_chunk(int g, int ci, int cmax) { return ci + 1 < nchunks(g, cmax) ? ci + 1 : 0; }
-
 }  // namespace
 }  // namespace stp
 
@@ -448,7 +275,7 @@ __host__ __device__ constexpr int next_chunk(int g, int ci, int cmax) { return c
 namespace stp {
 namespace {
 
-// Per-lane setup shared by the matrix-core chain and the residual kernel: stages E* and
+// Per-lane setup of the matrix-core chain: stages E* and
 // A^{j*} of the group, then per lane the sparse star row, the G coupling of
 // the lane's quantity, row u of (Z - E*_pp I)^-1 (to LDS) and the closure row
 // dr (to LDS); the dependency levels of the strict upper part G of E* only
@@ -1012,168 +839,6 @@ __global__ __launch_bounds__(Cfg<N>::kThreads) void mfma_solve_kernel(PredictArg
   });
 }
 
-// Float64 residual of the full element system for the current Q (the
-// matrix-free form of eq:stp-lineq after the multiplication with M^-1 S^-1,
-// section "Block-wise back-substitution"):
-//   r[p,n,u] = (S^-1 w)_u Q0[p,n] - sum_s Z_us Q[p,n,s] + sum_q E*_pq Q[q,n,u]
-//              - sum_j sum_q A^{j*}_pq sum_l Khat^j[n,l] Q[q,l,u],
-// written to `rout` in float (the right-hand side of the correction solve).
-// Same lane mapping and chunk order as the solve; the Khat term is the green
-// update of the solve applied to the known Q, accumulated in float64.  The
-// residual of a chunk is collected in LDS and written in contiguous runs.
-template <int N>
-__global__ __launch_bounds__(Cfg<N>::kThreads) void fused_residual_kernel(PredictArgs a, float* rout) {
-  using C = Cfg<N>;
-  using R = double;
-  constexpr int B = C::B, T = C::T, kE = C::kElems, kThreads = C::kThreads;
-  __shared__ Shared<N, R> sh;
-  R* const bufR = sh.u.c.bufB;  // residual of the chunk, same layout, to memory after the chunk
-  // Q of the chunks (and Q0 of the top-block chunks, [element][quantity][mode])
-  // alternate between two buffers: the X chunk buffer and the per-lane rows
-  // of the setup, which are not used after it.  Each chunk's loads are issued
-  // during the previous chunk and stored to its buffer before that chunk's
-  // green update, so only the first chunk waits for memory.  Where the second
-  // buffer does not fit, every chunk stages its own rows.
-  constexpr int kXSize = C::kBufSize, kQ0Size = C::kSlots * kNQ * C::kChunk;
-  constexpr bool kTwoBuffers = kXSize + 2 * kQ0Size <= 2 * C::kThreads * T;
-  static_assert(kQ0Size <= C::kThreads * T, "Q0 staging fits");
-  double* const rows = &sh.zr[0][0];  // zr and dr: 2 kThreads T contiguous doubles
-  auto xbuf = [&](int ci_index) -> R* { return (kTwoBuffers && (ci_index & 1)) ? rows : sh.u.c.bufX; };
-  auto q0buf = [&](int ci_index) -> double* {
-    return kTwoBuffers ? rows + kXSize + (ci_index & 1) * kQ0Size : rows;
-  };
-  const int tid = threadIdx.x;
-  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kE;
-  const int64_t nloc64 = a.n - e0 < kE ? a.n - e0 : kE;
-  const int nloc = static_cast<int>(nloc64);
-  const LaneId<N> lid(tid);
-  const int es = lid.es, p = lid.p, u = lid.u;
-  const bool active = es < nloc;
-  const int cb = C::blk(es, p);
-  const R* kv = khat_sparse<N, R>();
-  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int64_t erow = ((active ? e0 + es : 0) * kNQ + p);
-  const double w = sinv_w(u);
-
-  // rows below the top block, loaded after the setup so that its loads do
-  // not wait behind them
-  R r[C::LR];
-  LaneSetup<N, R> L;
-  L.run(sh, a, e0, nloc, tid, es, p, u, active, cb);
-  {
-    const double* q0row = a.Q0 + erow * B;
-#pragma unroll
-    for (int n = 0; n < C::LN; ++n) r[n] = q0row[n] * w;
-  }
-  const double zpp = sh.G[es][p][p];
-  const bool general_g = __builtin_amdgcn_readfirstlane(__syncthreads_or(active && L.gcount > 1)) != 0;
-  const int pb = C::blk(es, L.gp);
-  double zrow[T];  // row u of Z
-#pragma unroll
-  for (int v = 0; v < T; ++v) zrow[v] = z_entry(u, v);
-
-  static_for<0, N + 1>([&](auto gi) __attribute__((always_inline)) {
-    constexpr int g = N - decltype(gi)::value;
-    static_for<0, nchunks(g, C::kChunk)>([&](auto ci) __attribute__((always_inline)) {
-      constexpr int m0 = chunk_start(g, C::kChunk, decltype(ci)::value);
-      constexpr int c = chunk_size(g, C::kChunk, decltype(ci)::value);
-      constexpr int CI = chunk_index(N, g, decltype(ci)::value, C::kChunk);
-      R* const bufX = xbuf(CI);
-      double* const q0s = q0buf(CI);
-      if constexpr (g > 0) prefetch_columns<N, R, m0, c, kThreads / 64>(kv, wave);
-      // stage Q of the chunk (and Q0 of the top block) in LDS, coalesced,
-      // unless the previous chunk did
-      if constexpr (!kTwoBuffers || CI == 0) {
-        stage_rows<N, R, c * T>(bufX, static_cast<const double*>(a.Q), e0, m0 * T, nloc, tid);
-        if constexpr (g == N) {
-          Q0Stage<N, c> qs;
-          qs.issue(a.Q0, e0, m0, nloc, tid);
-          qs.commit(q0s, nloc, tid);
-        }
-      }
-      __syncthreads();
-      // loads of the next chunk, in flight during the local terms
-      constexpr bool kHasNext = !(g == 0 && decltype(ci)::value + 1 == nchunks(g, C::kChunk));
-      constexpr int gn = kHasNext ? next_block(g, decltype(ci)::value, C::kChunk) : 0;
-      constexpr int cin = kHasNext ? next_chunk(g, decltype(ci)::value, C::kChunk) : 0;
-      constexpr int mn = chunk_start(gn, C::kChunk, cin), cn = chunk_size(gn, C::kChunk, cin);
-      constexpr bool kPrefetch = kTwoBuffers && kHasNext;
-      RowStage<N, cn * T> nrows;
-      Q0Stage<N, cn> nq0;
-      if constexpr (kPrefetch) {
-        nrows.issue(static_cast<const double*>(a.Q), e0, mn * T, nloc, tid);
-        if constexpr (gn == N) nq0.issue(a.Q0, e0, mn, nloc, tid);
-      }
-      // local terms of the chunk's rows: their residual is now complete
-      static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-        constexpr int kk = decltype(k)::value;
-        constexpr int m = m0 + kk;
-        double base;
-        if constexpr (g == N) base = q0s[(es * kNQ + p) * c + kk] * w;
-        else base = r[m];
-        double zx = 0.0;
-#pragma unroll
-        for (int v = 0; v < T; ++v) zx = fma(zrow[v], bufX[cb + kk * T + v], zx);
-        double ex = zpp * bufX[cb + kk * T + u];
-        if (!general_g) {
-          ex = fma(L.gcoef, bufX[pb + kk * T + u], ex);
-        } else {
-          for (int q = p + 1; q < kNQ; ++q) {
-            const double gq = sh.G[es][p][q];
-            if (gq != 0.0) ex = fma(gq, bufX[C::blk(es, q) + kk * T + u], ex);
-          }
-        }
-        bufR[cb + kk * T + u] = base - zx + ex;
-      });
-      // the next chunk's rows to the other buffer (no wave reads it during
-      // this chunk)
-      if constexpr (kPrefetch) {
-        nrows.commit(xbuf(CI + 1), nloc, tid);
-        if constexpr (gn == N) nq0.commit(q0buf(CI + 1), nloc, tid);
-      }
-      // Khat term into the rows of lower blocks
-      if constexpr (g > 0) {
-        R kgrp[kGroup<R>];
-        load_first_group<N, m0, R>(kv, kgrp);
-        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-          constexpr int kk = decltype(k)::value;
-          R y0, y1, y2;
-          L.template star<kk>(bufX, a, e0, es, p, u, active, y0, y1, y2);
-          green_column<N, m0 + kk, (kk + 1 < c ? m0 + kk + 1 : -1), R>(r, y0, y1, y2, kv, kgrp);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      }
-      __syncthreads();  // before the next chunk overwrites the buffers
-      // the residual of the chunk to memory: every (element, quantity) row is
-      // one contiguous run of c*T floats (consecutive lanes, consecutive
-      // values), streaming stores; the next chunk writes the residual buffer
-      // only after its own barrier
-      {
-        constexpr int per = c * T;
-        constexpr int kGroupOut = 3;
-        constexpr int iters = (kE * kNQ * per + kThreads - 1) / kThreads;
-        constexpr int ngroups = (iters + kGroupOut - 1) / kGroupOut;
-        const int limit = nloc * kNQ * per;
-        float* const Rg = rout + e0 * (kNQ * B * T) + m0 * T;
-#pragma unroll 1
-        for (int gi = 0; gi < ngroups; ++gi) {
-          float v[kGroupOut];
-#pragma unroll
-          for (int k = 0; k < kGroupOut; ++k) {
-            const int i = tid + (gi * kGroupOut + k) * kThreads;
-            v[k] = static_cast<float>(bufR[C::rowblk(i / per) + i % per]);
-          }
-#pragma unroll
-          for (int k = 0; k < kGroupOut; ++k) {
-            const int i = tid + (gi * kGroupOut + k) * kThreads;
-            if (i < limit) __builtin_nontemporal_store(v[k], &Rg[(i / per) * (B * T) + i % per]);
-          }
-        }
-      }
-    });
-  });
-}
-
 }  // namespace
 
 template <>
@@ -1195,8 +860,7 @@ hipError_t launch_fused<STP_NQ, STP_DEGREE>(const PredictArgs& a, int precision,
     err = hipGetLastError();
   }
   for (int k = 0; k < refine_steps && err == hipSuccess; ++k) {
-    hipLaunchKernelGGL((fused_residual_kernel<N>), grid, block, 0, stream, a, workspace);
-    err = hipGetLastError();
+    err = launch_solve<N, double, kResidual>(a, workspace, stream);
     if (err != hipSuccess) break;
     if (valu_float_chain) {
       err = launch_solve<N, float, kCorrect>(a, workspace, stream);

@@ -134,7 +134,10 @@ struct SolveShared {
   using C = SolveCfg<N>;
   static constexpr int kTab = (khat_nnz<N>() + 15) / 16 * 16;
   R khat[kTab > 0 ? kTab : 16];            // Khat in usage order
-  double rows[C::kThreads][C::T];          // per lane: dense row of its dark-blue step
+  union {
+    double rows[C::kThreads][C::T];        // per lane: dense row of its dark-blue step
+    float res[(C::kPos + 1) * C::S];       // kResidual: residual of the chunk, blocks as in x
+  };
   double q0[(C::kPos + 1) * C::DN];        // Q0 of the top block
   int pos[C::kRows];
   int row[C::kPos + 1];                    // of a position (the general code's; -1: none)
@@ -182,17 +185,38 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int kInit = 0;     // b = Q0 (S^-1 w); Q <- X
-constexpr int kCorrect = 1;  // b = residual (float workspace); Q <- Q + X
+constexpr int kInit = 0;      // b = Q0 (S^-1 w); Q <- X
+constexpr int kCorrect = 1;   // b = residual (float workspace); Q <- Q + X
+constexpr int kResidual = 2;  // float workspace <- residual of the system for the X in Q
 
 constexpr unsigned kDenseStar = 1u, kGeneralE = 2u;
 
 // Algorithm 3 over a group of elements in precision R (the dark-blue solves
 // are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
-// b = the residual in `rin` (float), Q <- Q + X.
+// b = the residual in `work` (float), Q <- Q + X.
+//
+// kResidual: the float64 residual of the full element system for the current
+// Q (the matrix-free form of eq:stp-lineq after the multiplication with
+// M^-1 S^-1, section "Block-wise back-substitution"):
+//   r[p,n,u] = (S^-1 w)_u Q0[p,n] - sum_s Z_us Q[p,n,s] + sum_q E*_pq Q[q,n,u]
+//              - sum_j sum_q A^{j*}_pq sum_l Khat^j[n,l] Q[q,l,u],
+// written to `work` in float.  Its star and Khat products are the green
+// update applied to the known X, chunk by chunk from the top block down, so it
+// shares that code; X comes from Q one chunk ahead instead of from the
+// dark-blue step, and the local terms of a chunk's rows follow its barrier.
+// waves per SIMD the registers are held to: the residual keeps about 30 more
+// than the solve (X of the next chunk, a row of Z), so it gets one wave less
+// where they would spill (N = 5)
+template <int N, int Mode>
+constexpr int solve_occupancy() {
+  using C = SolveCfg<N>;
+  return Mode == kResidual && C::kWaves <= 4 && 512 / STP_SOLVE_OCC - 2 * C::LN <= 100 ? STP_SOLVE_OCC - 1 : STP_SOLVE_OCC;
+}
+
 template <int N, typename R, int Mode>
-__global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_kernel(PredictArgs a, const float* rin) {
+__global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())) void solve_kernel(PredictArgs a, float* work) {
   using C = SolveCfg<N>;
   using P = stp_gen::KhatPattern<N>;
   using ZS = stp_gen::ZinvSparse<N>;
@@ -270,7 +294,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
   const char* const Q0b = reinterpret_cast<const char*>(a.Q0 + e0 * (kNQ * B));
   char* const Qb = reinterpret_cast<char*>(a.Q + e0 * (kNQ * B * T));
   char* const Ib = reinterpret_cast<char*>(a.Qint ? a.Qint + e0 * (kNQ * B) : nullptr);
-  const char* const Rb = reinterpret_cast<const char*>(rin ? rin + e0 * (kNQ * B * T) : nullptr);
+  char* const Rb = reinterpret_cast<char*>(work ? work + e0 * (kNQ * B * T) : nullptr);
   const unsigned q0off = static_cast<unsigned>(arow * (B * 8));
   const unsigned ioff = q0off + 8 * u;
   const unsigned qoff = static_cast<unsigned>(arow * (B * T * 8) + 16 * u);
@@ -284,7 +308,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
   __syncthreads();
 
   // Q0 of the top block: each group its own row, to LDS below
-  constexpr int kQt = Mode == kInit ? (DN + T - 1) / T : 0;
+  constexpr int kQt = Mode != kCorrect ? (DN + T - 1) / T : 0;
   double qt[kQt > 0 ? kQt : 1];
 #pragma unroll
   for (int k = 0; k < kQt; ++k)
@@ -308,6 +332,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
 #pragma unroll
   for (int q = 1; q < kNQ; ++q) partner_coupled = partner_coupled || (q > gp && sh.u.s.G[es][gp][q] != 0.0);
   const int ppos = gcount ? sh.pos[es * kNQ + gp] : pos;
+  (void)partner_coupled;
   // Row u of (Z - E*_pp I)^-1: two entries of Z^-1 without a diagonal source;
   // otherwise a dense row from an elimination, done only by waves holding
   // such a lane.  xc = row . S^-1 w.
@@ -318,7 +343,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
   const int zc0 = ZS::col[2 * u], zc1 = ZS::col[2 * u + 1];
   double zv0 = ZS::val[2 * u], zv1 = ZS::val[2 * u + 1];
   double xc = fma(zv0, sinv_w(zc0), zv1 * sinv_w(zc1)), dc = 0.0;
-  {
+  if constexpr (Mode != kResidual) {
     double r[T];
 #pragma unroll
     for (int v = 0; v < T; ++v) r[v] = (zc0 == v ? zv0 : 0.0) + (zc1 == v ? zv1 : 0.0);
@@ -370,13 +395,16 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
   {
     const bool other_wave = ppos / GW != pos / GW;
     const unsigned f = (active && npop > kStarNnz ? kDenseStar : 0u) |
-                       (active && (gcount > 1 || (gcount == 1 && (partner_coupled || other_wave || z != 0.0))) ? kGeneralE : 0u);
+                       (active && (gcount > 1 || (Mode != kResidual && gcount == 1 && (partner_coupled || other_wave || z != 0.0)))
+                            ? kGeneralE
+                            : 0u);
     if (f) atomicOr(&sh.flags, f);
   }
   __syncthreads();
   const unsigned flags = __builtin_amdgcn_readfirstlane(sh.flags);
   const bool dense_star = (flags & kDenseStar) != 0, closure = (flags & kGeneralE) == 0;
-  if (!closure) {
+  if constexpr (Mode == kResidual) {
+  } else if (!closure) {
     // dependency levels of a general upper-triangular E (level = longest
     // coupling chain below a quantity), one thread per element
     if (tid < nloc) {
@@ -427,13 +455,13 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
 
   // rows of b below the top block, loaded after the setup (its elimination
   // needs the registers); float64 Q0 rows are scaled when they have arrived
-  constexpr bool kScaleLate = Mode == kInit && std::is_same_v<R, double>;
+  constexpr bool kScaleLate = Mode != kCorrect && std::is_same_v<R, double>;
   R b[C::LR];
   const double w_u = sinv_w(u);
 #pragma unroll
   for (int n = 0; n < LN; ++n) {
     if constexpr (kScaleLate) b[n] = load_q0(n);
-    else if constexpr (Mode == kInit) b[n] = static_cast<R>(load_q0(n) * w_u);
+    else if constexpr (Mode != kCorrect) b[n] = static_cast<R>(load_q0(n) * w_u);
     else b[n] = static_cast<R>(load_r(n));
   }
   LdsR* const xg = x0 + pos * S;            // the group's block
@@ -448,6 +476,24 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
 #pragma unroll
     for (int k = 0; k < kTop0; ++k) rtop[k] = static_cast<R>(load_r(LN + k));
   }
+
+  // kResidual: X of the next chunk, as the pairs of the output pass
+  constexpr int kPairs = (C::kChunk * T / 2 + T - 1) / T;
+  pair_t xpre[Mode == kResidual && kPairs > 0 ? kPairs : 1];
+  double xlast = 0.0;
+  auto load_chunk = [&](auto gc, auto cic) __attribute__((always_inline)) {
+    constexpr int gl = decltype(gc)::value, cil = decltype(cic)::value;
+    constexpr int m = chunk_start(gl, C::kChunk, cil), cl = chunk_size(gl, C::kChunk, cil);
+    constexpr int npl = cl * T / 2, nl = (npl + T - 1) / T;
+#pragma unroll
+    for (int j = 0; j < nl; ++j)
+      if ((j + 1) * T <= npl || j * T + u < npl)
+        xpre[j] = *reinterpret_cast<const pair_t*>(Qb + qoff + (m * T + j * 2 * T) * 8);
+    if constexpr ((cl * T) % 2 != 0) {
+      if (u == 0) xlast = *reinterpret_cast<const double*>(Qb + qoff + (m * T + cl * T - 1) * 8);
+    }
+  };
+  if constexpr (Mode == kResidual) load_chunk(ic<N>{}, ic<0>{});
 
   static_for<0, N + 1>([&](auto gi) __attribute__((always_inline)) {
     constexpr int g = N - decltype(gi)::value;
@@ -484,7 +530,17 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
         }
       }
       // ---- X of the chunk: dark-blue blocks and G coupling (float64)
-      if (Mode == kInit && g == N && closure) {
+      if constexpr (Mode == kResidual) {
+#pragma unroll
+        for (int j = 0; j < nst; ++j)
+          if ((j + 1) * T <= np || j * T + u < np) {
+            xo[xb + j * 2 * T] = xpre[j].x;
+            xo[xb + j * 2 * T + 1] = xpre[j].y;
+          }
+        if constexpr (odd) {
+          if (u == 0) xg[xb + c * T - 1] = xlast;
+        }
+      } else if (Mode == kInit && g == N && closure) {
         if (wave_coupled) {
 #pragma unroll
           for (int k = 0; k < c; ++k)
@@ -563,11 +619,64 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
         for (int n = 0; n < LN; ++n) b[n] *= w_u;
       }
       wave_fence();
-      if constexpr (green) __syncthreads();
+      if constexpr (green || Mode == kResidual) __syncthreads();
+      if constexpr (Mode == kResidual) {
+        if constexpr (cidx + 1 < nchunks(g, C::kChunk)) load_chunk(ic<g>{}, ic<cidx + 1>{});
+        else if constexpr (g > 0) load_chunk(ic<(g > 0 ? g - 1 : 0)>{}, ic<0>{});
+        // local terms of the chunk's rows: their residual is now complete
+        double zrow[T];  // row u of Z
+#pragma unroll
+        for (int v = 0; v < T; ++v) zrow[v] = z_entry(uc, v);
+#pragma unroll
+        for (int k = 0; k < c; ++k) {
+          double base, zx = 0.0;
+          if constexpr (g == N) base = qg[m0 - LN + k] * w_u;
+          else base = b[m0 + k];
+#pragma unroll
+          for (int v = 0; v < T; ++v) zx = fma(zrow[v], xg[xb + k * T + v], zx);
+          double ex = z * xl[xb + k * T];
+          if (closure) {
+            ex = fma(gcoef, xs[xb + k * T + uc], ex);
+          } else {
+            const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? kNQ : row - es * kNQ;
+            if (active) {
+#pragma unroll 1
+              for (int q = p + 1; q < kNQ; ++q) {
+                const double gq = a.dt * a.E[((e0 + es) * kNQ + p) * kNQ + q];
+                if (gq != 0.0) ex = fma(gq, x0[sh.pos[es * kNQ + q] * S + xb + k * T + uc], ex);
+              }
+            }
+          }
+          sh.res[pos * S + k * T + uc] = static_cast<float>(base - zx + ex);
+        }
+        wave_fence();
+      }
       // ---- outputs of the chunk from the group's own block: Q <- X or
       // Q <- Q + X, and Qint = dt X[:, :, 0]; issued after the green update
       // (the block lives until the chunk after the next)
       auto store_outputs = [&]() __attribute__((always_inline)) {
+        if constexpr (Mode == kResidual) {
+          // four consecutive values per lane
+          constexpr int n4 = c * T / 4, it4 = (n4 + T - 1) / T, rest = c * T - 4 * n4;
+          const float* const rg = sh.res + pos * S;
+          char* const dst = Rb + roff - 4 * uc + m0 * (T * 4);
+          if (active) {
+#pragma unroll
+            for (int j = 0; j < it4; ++j)
+              if ((j + 1) * T <= n4 || j * T + uc < n4) {
+                quad_t v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = rg[4 * (j * T + uc) + i];
+                *reinterpret_cast<quad_t*>(dst + 16 * (j * T + uc)) = v;
+              }
+            if constexpr (rest > 0) {
+#pragma unroll
+              for (int i = 0; i < (rest + T - 1) / T; ++i)
+                if (i * T + uc < rest) *reinterpret_cast<float*>(dst + 4 * (4 * n4 + i * T + uc)) = rg[4 * n4 + i * T + uc];
+            }
+          }
+          return;
+        }
         pair_t v[nst > 0 ? nst : 1];
         double last = 0.0, iv[nin];
 #pragma unroll
@@ -689,12 +798,12 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, STP_SOLVE_OCC) void solve_ke
 }
 
 template <int N, typename R, int Mode>
-hipError_t launch_solve(const PredictArgs& a, const float* rin, hipStream_t stream) {
+hipError_t launch_solve(const PredictArgs& a, float* work, hipStream_t stream) {
   using C = SolveCfg<N>;
   const int64_t groups = (a.n + C::kE - 1) / C::kE;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL((solve_kernel<N, R, Mode>), dim3(static_cast<unsigned>(groups)), dim3(C::kThreads), 0, stream, a,
-                     rin);
+                     work);
   return hipGetLastError();
 }
 
