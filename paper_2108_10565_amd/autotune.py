@@ -1,11 +1,12 @@
 """Autotuner of the solve kernel's tile shape per polynomial degree.
 
 The tile shape of degree N is (waves per workgroup, elements per workgroup,
-modes per chunk, waves per SIMD the registers are held to): how many elements
-one workgroup predicts together, how many modes of a degree block go through
-LDS at once, and how many waves share a SIMD.  They trade occupancy and lane
-use against LDS, registers and how widely Khat is shared, so the best shape is
-measured, not derived.
+modes per chunk, waves per SIMD the registers are held to, X buffers, modes per
+chunk of the correction and the residual): how many elements one workgroup
+predicts together, how many modes of a degree block go through LDS at once and
+with how many barriers, and how many waves share a SIMD.  They trade occupancy
+and lane use against LDS, registers and how widely Khat is shared, so the best
+shape is measured, not derived.
 
 Two phases, because kernels are compiled on the host and timed on the GPU:
 
@@ -39,14 +40,14 @@ import time
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 TUNE_DIR = os.path.join(PKG, "_tune")
-CANDIDATES = {0: [(1, 4, 1, 4), (2, 9, 1, 4), (4, 16, 1, 4)],
-              1: [(1, 2, 3, 4), (2, 4, 3, 4), (4, 9, 3, 4)],
-              2: [(1, 1, 6, 4), (2, 3, 3, 4), (2, 3, 6, 5), (4, 6, 6, 4), (5, 8, 6, 4)],
-              3: [(2, 2, 5, 4), (4, 4, 3, 4), (4, 4, 5, 4), (4, 4, 10, 4), (5, 6, 5, 4), (8, 9, 5, 4)],
-              4: [(4, 3, 3, 3), (4, 3, 5, 3), (4, 3, 8, 3), (7, 6, 5, 3), (8, 7, 5, 3), (12, 11, 5, 3)],
-              5: [(4, 3, 2, 3), (4, 3, 3, 3), (4, 3, 5, 2), (8, 6, 5, 2)],
-              6: [(4, 2, 10, 2), (8, 5, 7, 2), (8, 5, 8, 2), (8, 5, 10, 2)],
-              7: [(5, 3, 6, 2), (8, 4, 3, 2), (8, 4, 4, 2)]}
+CANDIDATES = {0: [(1, 4, 1, 2, 1, 1), (2, 9, 1, 2, 1, 1), (4, 16, 1, 2, 1, 1)],
+              1: [(1, 2, 3, 3, 1, 3), (2, 4, 3, 3, 1, 3), (4, 9, 3, 3, 1, 3)],
+              2: [(1, 1, 6, 4, 1, 6), (2, 3, 3, 4, 2, 6), (2, 3, 6, 4, 1, 6), (4, 6, 6, 4, 1, 6)],
+              3: [(4, 4, 5, 4, 2, 5), (4, 4, 10, 3, 1, 5), (5, 6, 5, 3, 2, 5), (8, 9, 5, 4, 2, 5)],
+              4: [(4, 3, 3, 3, 2, 5), (4, 3, 5, 3, 2, 5), (4, 3, 8, 3, 1, 5), (4, 3, 15, 2, 1, 5), (12, 11, 5, 3, 2, 5)],
+              5: [(4, 3, 2, 3, 2, 3), (4, 3, 3, 3, 2, 3), (4, 3, 5, 3, 1, 3), (8, 6, 5, 2, 2, 3)],
+              6: [(4, 2, 10, 2, 2, 10), (8, 5, 8, 2, 2, 10), (8, 5, 10, 2, 2, 10), (8, 5, 14, 2, 1, 10)],
+              7: [(8, 4, 3, 2, 2, 4), (8, 4, 4, 2, 2, 4), (8, 4, 6, 2, 1, 4)]}
 ELEMENTS = {0: 262144, 1: 262144, 2: 262144, 3: 262144, 4: 262144, 5: 262144, 6: 262144, 7: 65536}
 
 

@@ -67,8 +67,9 @@ def tile_table(path: str = TILES) -> dict:
 
 
 def solve_table(nq: int, path: str = TILES) -> dict:
-    """{degree: (waves, elements, chunk, waves per SIMD)} of the solve kernel for
-    nq quantities, as the autotuner wrote it."""
+    """{degree: (waves, elements, chunk, waves per SIMD, X buffers, chunk of the
+    correction and the residual)} of the solve kernel for nq quantities, as the
+    autotuner wrote it."""
     import json
     t = json.load(open(path))["solve"][str(nq)]
     return {int(n): tuple(int(x) for x in v) for n, v in t.items()}
@@ -85,11 +86,12 @@ def fused_object_name(nq: int, n: int) -> str:
 def fused_object_cmd(n: int, tile, solve, obj: str, nq: int = 13):
     """hipcc command compiling the fused kernels of degree n for nq quantities
     with one tile shape (tile: threads, chunk; solve: waves, elements, chunk,
-    waves per SIMD)."""
+    waves per SIMD, X buffers, chunk of the correction and the residual)."""
     return [HIPCC] + HIP_FLAGS + ["-x", "hip", f"-DSTP_NQ={nq}", f"-DSTP_DEGREE={n}",
                                   f"-DSTP_TILE_THREADS={tile[0]}", f"-DSTP_TILE_CHUNK={tile[1]}",
                                   f"-DSTP_SOLVE_WAVES={solve[0]}", f"-DSTP_SOLVE_ELEMS={solve[1]}",
-                                  f"-DSTP_SOLVE_CHUNK={solve[2]}", f"-DSTP_SOLVE_OCC={solve[3]}", "-c",
+                                  f"-DSTP_SOLVE_CHUNK={solve[2]}", f"-DSTP_SOLVE_OCC={solve[3]}",
+                                  f"-DSTP_SOLVE_BUFS={solve[4]}", f"-DSTP_SOLVE_CHUNK2={solve[5]}", "-c",
                                   os.path.join(CSRC, "kernel_fused.hip"), "-o", obj]
 
 

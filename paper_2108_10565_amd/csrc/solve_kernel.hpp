@@ -4,19 +4,23 @@
 //
 // What bounds it.  At N = 6 an element needs 1.0 MFLOP on the float64 vector
 // pipe (14.6 ns at the measured 70 TFLOP/s) and moves 84 KB (16.8 ns at the
-// measured 5 TB/s copy), so neither alone explains 50 ns: with one or two
+// measured 5 TB/s copy), so neither alone explains the 39 ns it takes (50 ns
+// with scalar-loaded Khat and workgroup-wide dark-blue steps): with one or two
 // waves per SIMD the time goes to latencies that nothing overlaps (scalar
 // loads of Khat, workgroup barriers, LDS round trips of the dark-blue step).
-// The layout below is chosen to remove those:
+// Of a workgroup's 117,000 cycles the green update takes 65,000 (43,000 at the
+// pipe's rate), X and its barriers 26,000, the setup 24,000.
+// The layout below is chosen to keep those latencies short:
 //
 // * Columns.  One lane per right-hand-side column (element e, quantity p,
 //   time mode u).  A wave holds whole (e, p) groups of T = N + 1 lanes,
 //   floor(64 / T) of them (63 of 64 lanes at T = 7), and a coupled quantity
 //   shares its wave with its partner (the poroelastic u, v, w <- uf, vf, wf).
 //   The dark-blue step and the G coupling therefore exchange data inside one
-//   wave, through LDS but without a workgroup barrier, and every chunk needs
-//   a single barrier: between its X and the star products that read X of the
-//   other quantities.  X alternates between two buffers.
+//   wave, through LDS but without a workgroup barrier; a chunk needs one
+//   barrier between its X and the star products that read X of the other
+//   quantities, and a second one before the next X where the tile has a single
+//   X buffer (SolveCfg).
 // * Khat.  The coefficients sit in LDS in usage order; one read brings 16 of
 //   them into one register pair (lane l holds coefficient l mod 16) and each
 //   multiply-add picks its own with a row broadcast (DPP row_newbcast), at
@@ -28,6 +32,11 @@
 // * Top block.  b = Q0 (S^-1 w) there, so X = Q0 (row of Zinv . S^-1 w) (and
 //   the same product with the closure row for a coupled quantity) is one or
 //   two products per value, without an exchange.
+// * Setup.  The columns of a star row are found with one ballot per group, a
+//   lane's row of the dark-blue inverse by elimination and back substitution
+//   of one right-hand side, and Q0 is read once per group and staged through
+//   the group's X blocks (it was read again by each of the T lanes): N = 7,
+//   16,384 elements 1.57 -> 1.43 ms, N = 5, 65,536 elements 1.35 -> 1.22 ms.
 // * Outputs.  A group's lanes store pairs of consecutive doubles of its own
 //   row (16 bytes per lane, T lanes contiguous): no index arithmetic, any
 //   chunk size.  Ordinary stores: streaming stores of these 112-byte pieces
@@ -44,26 +53,40 @@
 #pragma once
 
 // Tile of this degree: waves and elements per workgroup, modes per chunk,
-// waves per SIMD the registers are held to.
-#if !defined(STP_SOLVE_WAVES) || !defined(STP_SOLVE_ELEMS) || !defined(STP_SOLVE_CHUNK) || !defined(STP_SOLVE_OCC)
+// waves per SIMD the registers are held to, X buffers, and modes per chunk of
+// the correction and the residual (always two buffers).
+#if !defined(STP_SOLVE_WAVES) || !defined(STP_SOLVE_ELEMS) || !defined(STP_SOLVE_CHUNK) || !defined(STP_SOLVE_OCC) || \
+    !defined(STP_SOLVE_BUFS) || !defined(STP_SOLVE_CHUNK2)
 #error "compile with the solve tile of the build's table"
 #endif
 
 namespace stp {
 namespace {
 
-template <int N>
+constexpr int kInit = 0;      // b = Q0 (S^-1 w); Q <- X
+constexpr int kCorrect = 1;   // b = residual (float workspace); Q <- Q + X
+constexpr int kResidual = 2;  // float workspace <- residual of the system for the X in Q
+
+template <int N, int Mode>
 struct SolveCfg {
   static constexpr int B = n_modes(N), T = N + 1;
   static constexpr int LN = block_start(N);        // register-resident rows (below the top block)
   static constexpr int LR = LN > 0 ? LN : 1;
   static constexpr int DN = block_size(N);
   static constexpr int kWaves = STP_SOLVE_WAVES, kThreads = 64 * kWaves, kE = STP_SOLVE_ELEMS;
+  static constexpr bool kAlone = kWaves == 4 * STP_SOLVE_OCC;  // one workgroup fills the compute unit
   static constexpr int GW = 64 / T;                // groups of T lanes per wave
   static constexpr int kPos = kWaves * GW;         // group positions of the workgroup
   static constexpr int kRows = kE * kNQ;           // (element, quantity) rows
   static_assert(kRows <= kPos, "the elements must fit the workgroup's positions");
-  static constexpr int kChunk = STP_SOLVE_CHUNK < DN ? STP_SOLVE_CHUNK : DN;
+  // Modes per chunk and X buffers.  Two buffers: X of the next chunk is
+  // written while others still read this one's, one barrier per chunk.  One
+  // buffer takes a second barrier, but twice the modes fit, so there are half
+  // as many exchanges (N = 3, 262,144 elements: float64 1.21 against 1.24 ms,
+  // float32 chain 1.02 against 1.18; N = 5 keeps two, 1.23 against 1.35).
+  static constexpr int kBufs = Mode == kInit ? STP_SOLVE_BUFS : 2;
+  static constexpr int kChunkTile = Mode == kInit ? STP_SOLVE_CHUNK : STP_SOLVE_CHUNK2;
+  static constexpr int kChunk = kChunkTile < DN ? kChunkTile : DN;
   // X buffers: one block of S values per position.  S = T mod 16, so that the
   // address of lane (position, u) is congruent to T position + u: consecutive
   // lanes of a wave fall on consecutive banks.
@@ -84,7 +107,7 @@ struct SolveCfg {
 // (2).
 template <int N>
 struct SolveLayout {
-  using C = SolveCfg<N>;
+  using C = SolveCfg<N, kInit>;
   short row[C::kPos];
   short pos[C::kRows];
   constexpr SolveLayout() : row(), pos() {
@@ -124,19 +147,19 @@ template <int N>
 constexpr int khat_nnz() {
   using P = stp_gen::KhatPattern<N>;
   int n = 0;
-  for (int m = 0; m < SolveCfg<N>::B; ++m)
+  for (int m = 0; m < n_modes(N); ++m)
     n = P::col_start[m] + P::col_count[m] > n ? P::col_start[m] + P::col_count[m] : n;
   return n;
 }
 
-template <int N, typename R>
+template <int N, typename R, int Mode>
 struct SolveShared {
-  using C = SolveCfg<N>;
+  using C = SolveCfg<N, Mode>;
   static constexpr int kTab = (khat_nnz<N>() + 15) / 16 * 16;
   R khat[kTab > 0 ? kTab : 16];            // Khat in usage order
   union {
     double rows[C::kThreads][C::T];        // per lane: dense row of its dark-blue step
-    float res[(C::kPos + 1) * C::S];       // kResidual: residual of the chunk, blocks as in x
+    float res[Mode == kResidual ? (C::kPos + 1) * C::S : 1];  // residual of the chunk, blocks as in x
   };
   double q0[(C::kPos + 1) * C::DN];        // Q0 of the top block
   int pos[C::kRows];
@@ -149,7 +172,7 @@ struct SolveShared {
       double G[C::kE][kNQ][kNQ];           // E* (lower part zeroed)
       double A[C::kE][3][kNQ][kNQ];        // -A^{j*}: the green update then adds Khat y
     } s;
-    R x[2 * C::kBuf + 2 * C::T * C::T];    // X of two chunks (+ what the last lanes' output reads may run over)
+    R x[C::kBufs * C::kBuf + 2 * C::T * C::T];  // X of the chunks (+ what the last lanes' output reads may run over)
   } u;
 };
 
@@ -177,6 +200,59 @@ constexpr bool zinv_columns() {
   return true;
 }
 
+// Row u of (Z - z I)^-1: the solution y of (Z - z I)^T y = e_u by elimination
+// without pivoting and back substitution.  For z = dt E_pp < 0.5 (the range
+// stp_validate admits) the pivots stay away from zero: over z in [-1e7, 0.5)
+// and every degree N <= 7 the smallest is at least 3% of max|Z| + |z| (checked
+// numerically).
+template <int T>
+__device__ __forceinline__ void zinv_row(double z, int u, double (&y)[T]) {
+  double m[T][T], inv[T];
+#pragma unroll
+  for (int r = 0; r < T; ++r) {
+#pragma unroll
+    for (int c = 0; c < T; ++c) m[r][c] = z_entry(c, r) - (r == c ? z : 0.0);  // transpose
+    y[r] = r == u ? 1.0 : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < T; ++k) {
+    inv[k] = 1.0 / m[k][k];
+#pragma unroll
+    for (int r = k + 1; r < T; ++r) {
+      const double f = m[r][k] * inv[k];
+#pragma unroll
+      for (int c = k + 1; c < T; ++c) m[r][c] = fma(-f, m[k][c], m[r][c]);
+      y[r] = fma(-f, y[k], y[r]);
+    }
+  }
+#pragma unroll
+  for (int k = T - 1; k >= 0; --k) {
+#pragma unroll
+    for (int c = k + 1; c < T; ++c) y[k] = fma(-m[k][c], y[c], y[k]);
+    y[k] *= inv[k];
+  }
+}
+
+// Bit q of the result: f(q) for the lane's group, each lane of the group
+// having evaluated it for q = u, u + T, ... only (the lanes of a group would
+// all evaluate the same kNQ values otherwise).
+template <int T, class F>
+__device__ __forceinline__ unsigned group_mask(int grp, int u, F&& f) {
+  unsigned mask = 0;
+  if constexpr (T == 1) {  // nothing to share
+#pragma unroll
+    for (int q = 0; q < kNQ; ++q) mask |= f(q) ? 1u << q : 0u;
+    return mask;
+  }
+#pragma unroll
+  for (int q0 = 0; q0 < kNQ; q0 += T) {
+    const int q = q0 + u < kNQ ? q0 + u : kNQ - 1;
+    const unsigned long long bits = __builtin_amdgcn_ballot_w64(q0 + u < kNQ && f(q));
+    mask |= (static_cast<unsigned>(bits >> (grp * T)) & ((1u << T) - 1)) << q0;
+  }
+  return mask;
+}
+
 // Orders the LDS accesses of one wave (a wave's LDS operations complete in
 // order; this keeps the compiler from reordering them).
 __device__ __forceinline__ void wave_fence() {
@@ -186,10 +262,6 @@ __device__ __forceinline__ void wave_fence() {
 
 typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
-
-constexpr int kInit = 0;      // b = Q0 (S^-1 w); Q <- X
-constexpr int kCorrect = 1;   // b = residual (float workspace); Q <- Q + X
-constexpr int kResidual = 2;  // float workspace <- residual of the system for the X in Q
 
 constexpr unsigned kDenseStar = 1u, kGeneralE = 2u;
 
@@ -211,20 +283,20 @@ constexpr unsigned kDenseStar = 1u, kGeneralE = 2u;
 // where they would spill (N = 5)
 template <int N, int Mode>
 constexpr int solve_occupancy() {
-  using C = SolveCfg<N>;
+  using C = SolveCfg<N, Mode>;
   return Mode == kResidual && C::kWaves <= 4 && 512 / STP_SOLVE_OCC - 2 * C::LN <= 100 ? STP_SOLVE_OCC - 1 : STP_SOLVE_OCC;
 }
 
 template <int N, typename R, int Mode>
-__global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())) void solve_kernel(PredictArgs a, float* work) {
-  using C = SolveCfg<N>;
+__global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, Mode>())) void solve_kernel(PredictArgs a, float* work) {
+  using C = SolveCfg<N, Mode>;
   using P = stp_gen::KhatPattern<N>;
   using ZS = stp_gen::ZinvSparse<N>;
   using LdsR = __attribute__((address_space(3))) R;
   using LdsD = __attribute__((address_space(3))) double;
   constexpr int B = C::B, T = C::T, kE = C::kE, kThreads = C::kThreads, S = C::S, GW = C::GW, DN = C::DN, LN = C::LN;
   static_assert(zinv_columns<N>(), "two-entry rows of Z^-1");
-  __shared__ SolveShared<N, R> sh;
+  __shared__ SolveShared<N, R, Mode> sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kE;
@@ -238,7 +310,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
   // LDS store, so the group waits for one memory latency)
   constexpr int kEIt = (kE * kNQ * kNQ + kThreads - 1) / kThreads;
   constexpr int kAIt = (3 * kE * kNQ * kNQ + kThreads - 1) / kThreads;
-  constexpr int nnz = khat_nnz<N>(), kTab = SolveShared<N, R>::kTab, kKIt = (kTab + kThreads - 1) / kThreads;
+  constexpr int nnz = khat_nnz<N>(), kTab = SolveShared<N, R, Mode>::kTab, kKIt = (kTab + kThreads - 1) / kThreads;
   {
     double ev[kEIt], av[kAIt];
     R kv[kKIt > 0 ? kKIt : 1];
@@ -305,32 +377,21 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
   auto load_r = [&](int m) __attribute__((always_inline)) {
     return *reinterpret_cast<const float*>(Rb + roff + m * (T * 4));
   };
-  __syncthreads();
-
-  // Q0 of the top block: each group its own row, to LDS below
-  constexpr int kQt = Mode != kCorrect ? (DN + T - 1) / T : 0;
+  // Q0 of this group's row, each lane every T-th mode (to LDS below)
+  constexpr int kQt = Mode != kCorrect ? (B + T - 1) / T : 0;
   double qt[kQt > 0 ? kQt : 1];
 #pragma unroll
   for (int k = 0; k < kQt; ++k)
-    qt[k] = k * T + u < DN ? *reinterpret_cast<const double*>(Q0b + ioff + (LN + k * T) * 8) : 0.0;
+    qt[k] = k * T + u < B ? *reinterpret_cast<const double*>(Q0b + ioff + k * T * 8) : 0.0;
+  __syncthreads();
+
   // G coupling of this lane's quantity (the first non-zero right of the
   // diagonal and their count), and whether that partner couples further
-  int gcount = 0, gp = p;
-  double gcoef = 0.0;
-#pragma unroll
-  for (int q = 1; q < kNQ; ++q) {
-    const double gq = sh.u.s.G[es][p][q];
-    if (valid && q > p && gq != 0.0) {
-      if (gcount == 0) {
-        gcoef = gq;
-        gp = q;
-      }
-      ++gcount;
-    }
-  }
-  bool partner_coupled = false;
-#pragma unroll
-  for (int q = 1; q < kNQ; ++q) partner_coupled = partner_coupled || (q > gp && sh.u.s.G[es][gp][q] != 0.0);
+  const unsigned gmask = group_mask<T>(grp, u, [&](int q) { return valid && q > p && sh.u.s.G[es][p][q] != 0.0; });
+  const int gcount = __builtin_popcount(gmask), gp = gmask ? __builtin_ctz(gmask) : p;
+  const double gcoef = gmask ? sh.u.s.G[es][p][gp] : 0.0;
+  const bool partner_coupled =
+      group_mask<T>(grp, u, [&](int q) { return valid && gmask && q > gp && sh.u.s.G[es][gp][q] != 0.0; }) != 0;
   const int ppos = gcount ? sh.pos[es * kNQ + gp] : pos;
   (void)partner_coupled;
   // Row u of (Z - E*_pp I)^-1: two entries of Z^-1 without a diagonal source;
@@ -348,10 +409,8 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
 #pragma unroll
     for (int v = 0; v < T; ++v) r[v] = (zc0 == v ? zv0 : 0.0) + (zc1 == v ? zv1 : 0.0);
     if (wave_stiff) {
-      double e_u[T], zs[T];
-#pragma unroll
-      for (int v = 0; v < T; ++v) e_u[v] = (v == u) ? 1.0 : 0.0;
-      zt_solve<T>(z, e_u, zs);
+      double zs[T];
+      zinv_row<T>(z, u, zs);
       if (z != 0.0) {
         xc = 0.0;
 #pragma unroll
@@ -367,12 +426,9 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
   // sparse row p of the three star matrices: the columns with a non-zero in
   // any direction, in ascending order
   __builtin_amdgcn_sched_barrier(0);  // the elimination's registers are free before these are taken
-  unsigned mask = 0;
-#pragma unroll
-  for (int q = 0; q < kNQ; ++q) {
-    const double v0 = sh.u.s.A[es][0][p][q], v1 = sh.u.s.A[es][1][p][q], v2 = sh.u.s.A[es][2][p][q];
-    if (valid && (v0 != 0.0 || v1 != 0.0 || v2 != 0.0)) mask |= 1u << q;
-  }
+  unsigned mask = group_mask<T>(grp, u, [&](int q) {
+    return valid && (sh.u.s.A[es][0][p][q] != 0.0 || sh.u.s.A[es][1][p][q] != 0.0 || sh.u.s.A[es][2][p][q] != 0.0);
+  });
   const int npop = __builtin_popcount(mask);
   // columns the wave's longest row needs (wave-uniform: 2, 4 or 6)
   const int ns = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(npop > 4)   ? 6
@@ -448,23 +504,37 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
       zv0 = zv1 = 0.0;
     }
   }
-#pragma unroll
-  for (int k = 0; k < kQt; ++k)
-    if (k * T + u < DN) sh.q0[pos * DN + k * T + u] = qt[k];
-  wave_fence();
-
-  // rows of b below the top block, loaded after the setup (its elimination
-  // needs the registers); float64 Q0 rows are scaled when they have arrived
-  constexpr bool kScaleLate = Mode != kCorrect && std::is_same_v<R, double>;
+  // Rows of b below the top block (after the setup: its elimination needs the
+  // registers).  b = Q0 (S^-1 w): the group's lanes share one row of Q0, which
+  // they loaded together; it goes through the group's own blocks of the X
+  // buffers, still unused, instead of T lanes loading the same values (at N = 6
+  // that took 3,600 cycles of the compute unit's load path per workgroup).
+  // Modes that do not fit the blocks are loaded by every lane.
+  LdsR* const xg = x0 + pos * S;            // the group's block
   R b[C::LR];
   const double w_u = sinv_w(u);
+  if constexpr (Mode != kCorrect) {
+    constexpr int kFit = (S * static_cast<int>(sizeof(R)) - (8 - static_cast<int>(sizeof(R)))) / 8;  // doubles per block
+    constexpr int kStaged = LN < C::kBufs * kFit ? LN : C::kBufs * kFit;
+    auto aligned = [&](int i) { return (LdsD*)(x0 + (sizeof(R) == 8 ? i : (i + 1) & ~1)); };
+    LdsD* const s0 = aligned(pos * S);
+    LdsD* const s1 = aligned((C::kBufs - 1) * C::kBuf + pos * S);
 #pragma unroll
-  for (int n = 0; n < LN; ++n) {
-    if constexpr (kScaleLate) b[n] = load_q0(n);
-    else if constexpr (Mode != kCorrect) b[n] = static_cast<R>(load_q0(n) * w_u);
-    else b[n] = static_cast<R>(load_r(n));
+    for (int k = 0; k < kQt; ++k) {
+      const int m = k * T + u;
+      if (m >= LN && m < B) sh.q0[pos * DN + m - LN] = qt[k];
+      if (m < kFit && m < kStaged) s0[m] = qt[k];
+      if (m >= kFit && m < kStaged) s1[m - kFit] = qt[k];
+    }
+    wave_fence();
+#pragma unroll
+    for (int n = 0; n < LN; ++n)
+      b[n] = static_cast<R>((n < kStaged ? (n < kFit ? s0[n] : s1[n - kFit]) : load_q0(n)) * w_u);
+    wave_fence();
+  } else {
+#pragma unroll
+    for (int n = 0; n < LN; ++n) b[n] = static_cast<R>(load_r(n));
   }
-  LdsR* const xg = x0 + pos * S;            // the group's block
   LdsR* const xs = x0 + ppos * S;           // what the dense row applies to
   LdsD* const qg = (LdsD*)&sh.q0[0] + pos * DN;
   LdsD* const qp = (LdsD*)&sh.q0[0] + ppos * DN;
@@ -500,7 +570,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
     static_for<0, nchunks(g, C::kChunk)>([&](auto ci) __attribute__((always_inline)) {
       constexpr int cidx = decltype(ci)::value;
       constexpr int m0 = chunk_start(g, C::kChunk, cidx), c = chunk_size(g, C::kChunk, cidx);
-      constexpr int xb = (chunk_index(N, g, cidx, C::kChunk) & 1) * C::kBuf;
+      constexpr int CI = chunk_index(N, g, cidx, C::kChunk), xb = (CI & (C::kBufs - 1)) * C::kBuf;
       constexpr int np = c * T / 2, nst = (np + T - 1) / T, nin = (c + T - 1) / T;
       constexpr bool odd = (c * T) % 2 != 0, green = g > 0;
       // the lane's addresses, formed anew for each chunk (an opaque copy of
@@ -529,6 +599,7 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
               iprev[k] = *reinterpret_cast<const double*>(Ib + ioff + (m0 + k * T) * 8);
         }
       }
+      if constexpr (C::kBufs == 1 && CI > 0) __syncthreads();  // the reads of the chunk before
       // ---- X of the chunk: dark-blue blocks and G coupling (float64)
       if constexpr (Mode == kResidual) {
 #pragma unroll
@@ -613,11 +684,6 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
 #pragma unroll
         for (int k = 0; k < cn; ++k) rtop[k] = static_cast<R>(load_r(mn + k));
       }
-      if constexpr (kScaleLate && green && g == N && cidx == 0) {
-        // b[p, n, u] = Q0[p, n] (S^-1 w)_u (eq:b_pmu)
-#pragma unroll
-        for (int n = 0; n < LN; ++n) b[n] *= w_u;
-      }
       wave_fence();
       if constexpr (green || Mode == kResidual) __syncthreads();
       if constexpr (Mode == kResidual) {
@@ -652,8 +718,12 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
         wave_fence();
       }
       // ---- outputs of the chunk from the group's own block: Q <- X or
-      // Q <- Q + X, and Qint = dt X[:, :, 0]; issued after the green update
-      // (the block lives until the chunk after the next)
+      // Q <- Q + X, and Qint = dt X[:, :, 0] (the block lives until the chunk
+      // after the next).  Issued after the green update, where the lane has
+      // registers to spare, except where one workgroup fills the compute unit:
+      // its waves would all be storing at once there, with no one's
+      // multiply-adds to cover it (N = 6: 2.73 ms against 2.67 ms after the
+      // first mode; N = 5, several workgroups: 1.22 against 1.25 ms).
       auto store_outputs = [&]() __attribute__((always_inline)) {
         if constexpr (Mode == kResidual) {
           // four consecutive values per lane
@@ -790,16 +860,20 @@ __global__ __launch_bounds__(SolveCfg<N>::kThreads, (solve_occupancy<N, Mode>())
           });
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (kk + 1 < c) star(ic<kk + 1>{});
+          if constexpr (C::kAlone && kk == 0) {
+            store_outputs();
+            __builtin_amdgcn_sched_barrier(0);
+          }
         });
       }
-      store_outputs();
+      if constexpr (!green || !C::kAlone) store_outputs();
     });
   });
 }
 
 template <int N, typename R, int Mode>
 hipError_t launch_solve(const PredictArgs& a, float* work, hipStream_t stream) {
-  using C = SolveCfg<N>;
+  using C = SolveCfg<N, Mode>;
   const int64_t groups = (a.n + C::kE - 1) / C::kE;
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL((solve_kernel<N, R, Mode>), dim3(static_cast<unsigned>(groups)), dim3(C::kThreads), 0, stream, a,
