@@ -1,8 +1,8 @@
-"""The corrector's two splits of an element over waves: few elements (the
-output tiles spread over waves, the split the oracle tests of the corrector
-run) and more than one per SIMD, with a last workgroup that is not full.  The
-same elements in copies of one mesh must give the same result in both.  Both
-accumulate every output over the same terms in the same order, so they may
+"""The corrector's splits of an element over waves: few elements (the output
+tiles spread over waves, the split the oracle tests of the corrector run) and
+more than one per SIMD (13 copies of the mesh where degree 7 takes a third
+split), with a last workgroup that is not full.  The same elements in copies
+of one mesh must give the same result in all.  They accumulate every output over the same terms in the same order, so they may
 differ by the rounding of a few hundred products at most: 1e-13 of the norm."""
 import numpy as np
 import pytest
@@ -17,9 +17,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nq", [13, 6])
-@pytest.mark.parametrize("N", range(8))
-def test_both_splits_agree(N, nq):
-    print(f"[gpu] corrector splits N={N} nq={nq}", flush=True)
+@pytest.mark.parametrize("N,copies", [(N, 4) for N in range(8)] + [(7, 13)])
+def test_splits_agree(N, copies, nq):
+    print(f"[gpu] corrector splits N={N} nq={nq} copies={copies}", flush=True)
     M = pmesh.periodic_cube(4)
     n, rng = M.n, np.random.default_rng(700 + N)
     if nq == 13:
@@ -31,9 +31,9 @@ def test_both_splits_agree(N, nq):
     Q = torch.from_numpy(rng.standard_normal((n, nq, s.B))).cuda()
     Qint = torch.from_numpy(1e-6 * rng.standard_normal((n, nq, s.B))).cuda()
     ref = s.correct(Q.clone(), Qint)
-    # four copies of the mesh and three more elements of the last copy: 1,283
-    idx = torch.cat([torch.arange(n)] * 4 + [torch.arange(3)]).cuda()
-    shift = n * torch.cat([torch.arange(4).repeat_interleave(n), torch.full((3,), 3)]).cuda()
+    # copies of the mesh and three more elements of the last copy: 1,283 or 4,163
+    idx = torch.cat([torch.arange(n)] * copies + [torch.arange(3)]).cuda()
+    shift = n * torch.cat([torch.arange(copies).repeat_interleave(n), torch.full((3,), copies - 1)]).cuda()
     for name in ("star", "E", "Gp", "Gm", "nb_code"):
         setattr(s, name, getattr(s, name)[idx].contiguous())
     s.neighbor = (s.neighbor[idx] + shift[:, None]).to(torch.int32).contiguous()
