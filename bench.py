@@ -157,8 +157,10 @@ def measured_traffic(workload: str):
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = os.path.join(ROOT, "paper_2108_10565_amd", "csrc", "kernel_fused.hip")
-    if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec.get("kernel_fused_sha256"):
+    sha = hashlib.sha256()
+    for name in ("kernel_fused.hip", "solve_kernel.hpp"):
+        sha.update(open(os.path.join(ROOT, "paper_2108_10565_amd", "csrc", name), "rb").read())
+    if sha.hexdigest() != rec.get("kernel_sources_sha256"):
         return None
     return rec["hbm_bytes_per_launch"]
 

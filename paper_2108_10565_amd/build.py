@@ -60,7 +60,7 @@ TILES = os.path.join(PKG, "tiles.json")
 
 
 def tile_table(path: str = TILES) -> dict:
-    """{degree: (threads, chunk)} of the residual kernel and the matrix-core chain."""
+    """{degree: (threads, chunk)} of the matrix-core chain."""
     import json
     t = json.load(open(path))["tiles"]
     return {int(n): (int(v[0]), int(v[1])) for n, v in t.items()}
