@@ -44,8 +44,8 @@ CANDIDATES = {0: [(1, 4, 1, 2, 1, 1), (2, 9, 1, 2, 1, 1), (4, 16, 1, 2, 1, 1)],
               1: [(1, 2, 3, 3, 1, 3), (2, 4, 3, 3, 1, 3), (4, 9, 3, 3, 1, 3)],
               2: [(1, 1, 6, 4, 1, 6), (2, 3, 3, 4, 2, 6), (2, 3, 6, 4, 1, 6), (4, 6, 6, 4, 1, 6)],
               3: [(4, 4, 5, 4, 2, 5), (4, 4, 10, 3, 1, 5), (5, 6, 5, 3, 2, 5), (8, 9, 5, 4, 2, 5)],
-              4: [(4, 3, 3, 3, 2, 5), (4, 3, 5, 3, 2, 5), (4, 3, 8, 3, 1, 5), (4, 3, 15, 2, 1, 5), (12, 11, 5, 3, 2, 5)],
-              5: [(4, 3, 2, 3, 2, 3), (4, 3, 3, 3, 2, 3), (4, 3, 5, 3, 1, 3), (8, 6, 5, 2, 2, 3)],
+              4: [(4, 3, 3, 3, 2, 5), (4, 3, 5, 3, 2, 5), (4, 3, 10, 3, 1, 7), (4, 3, 15, 2, 1, 7), (12, 11, 5, 3, 2, 5)],
+              5: [(4, 3, 2, 3, 2, 3), (4, 3, 3, 3, 2, 3), (4, 3, 9, 3, 1, 3), (8, 6, 5, 2, 2, 3)],
               6: [(4, 2, 10, 2, 2, 10), (8, 5, 8, 2, 2, 10), (8, 5, 10, 2, 2, 10), (8, 5, 14, 2, 1, 10)],
               7: [(8, 4, 3, 2, 2, 4), (8, 4, 4, 2, 2, 4), (8, 4, 6, 2, 1, 4)]}
 ELEMENTS = {0: 262144, 1: 262144, 2: 262144, 3: 262144, 4: 262144, 5: 262144, 6: 262144, 7: 65536}

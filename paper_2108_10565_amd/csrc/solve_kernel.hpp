@@ -83,7 +83,8 @@ struct SolveCfg {
   // written while others still read this one's, one barrier per chunk.  One
   // buffer takes a second barrier, but twice the modes fit, so there are half
   // as many exchanges (N = 3, 262,144 elements: float64 1.21 against 1.24 ms,
-  // float32 chain 1.02 against 1.18; N = 5 keeps two, 1.23 against 1.35).
+  // float32 chain 1.02 against 1.18; N = 5, 262,144: 4.68 against 4.95 with 9
+  // modes instead of 3; N = 7 keeps two, 1.43 against 1.72 at 16,384).
   static constexpr int kBufs = Mode == kInit ? STP_SOLVE_BUFS : 2;
   static constexpr int kChunkTile = Mode == kInit ? STP_SOLVE_CHUNK : STP_SOLVE_CHUNK2;
   static constexpr int kChunk = kChunkTile < DN ? kChunkTile : DN;
