@@ -22,8 +22,8 @@
 //      u <- uf, v <- vf, w <- wf) uses the closed form
 //      X_o = Zinv_o (b_o + G_op X_p) = zr . b_o + dr . b_p,
 //      dr = G_op (row of Zinv_o) Zinv_p, so no extra round is needed; any
-//      other upper-triangular E is handled level by level (level = longest
-//      coupling chain below a quantity);
+//      other coupled quantity follows level by level (level = longest
+//      coupling chain below it);
 //   2. outputs: X to Q and dt X[:, :, 0] to Qint;
 //   3. green blocks: every lane reads X[q, m, u] of the quantities in its
 //      star row, forms y_1..y_3 with its row of A^{1*}, A^{2*}, A^{3*}, and

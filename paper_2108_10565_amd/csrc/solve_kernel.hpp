@@ -45,11 +45,16 @@
 //   compute unit, so that one group's setup and barriers overlap another's
 //   multiply-adds (the tile table of the build).
 //
-// Inputs outside the fast forms take general code in the same kernel, chosen
-// per workgroup: a star row with more than kStarNnz columns reads the dense
-// rows from memory, and an E whose couplings are not of the closure form (or
-// whose partner sits in another wave) is solved level by level with a
-// barrier per level.
+// Inputs outside the fast forms take further code in the same kernel, chosen
+// per workgroup.  A star row with more than kStarNnz columns reads the dense
+// rows from memory.  A coupled quantity of the closure form (one coupling, to
+// a quantity without couplings, and no source of its own) whose partner sits
+// in another wave costs two more barriers per chunk (N = 6, 16,384 elements
+// with one such coupling: 690 us, 695 without it).  Every other coupled
+// quantity is late: its X follows in rounds after the others', one per level
+// of the dependency chain and chunk (one late quantity 870 us, twelve levels
+// of full rows 2.6 ms); that code stands out of the way of the ordinary case,
+// which it cost 3% between the chunks.
 #pragma once
 
 // Tile of this degree: waves and elements per workgroup, modes per chunk,
@@ -157,15 +162,24 @@ template <int N, typename R, int Mode>
 struct SolveShared {
   using C = SolveCfg<N, Mode>;
   static constexpr int kTab = (khat_nnz<N>() + 15) / 16 * 16;
+  static constexpr int kCoupled = C::kE * kNQ * (kNQ - 1) / 2;  // entries of E* right of the diagonal
+  // where a general E keeps them: after X, or in the residual, whose two X
+  // buffers fill the LDS at N = 6, with its output where the rows leave room
+  static constexpr int kRes = Mode == kResidual ? (C::kPos + 1) * C::S : 1;
+  static constexpr bool kInRows = Mode == kResidual && 8 * kCoupled + 4 * kRes <= 8 * C::kThreads * C::T;
   R khat[kTab > 0 ? kTab : 16];            // Khat in usage order
   union {
     double rows[C::kThreads][C::T];        // per lane: dense row of its dark-blue step
-    float res[Mode == kResidual ? (C::kPos + 1) * C::S : 1];  // residual of the chunk, blocks as in x
+    struct {
+      double G[kInRows ? kCoupled : 1];    // as u.c.G
+      float res[kRes];                     // residual of the chunk, blocks as in x
+    } r;
   };
   double q0[(C::kPos + 1) * C::DN];        // Q0 of the top block
   int pos[C::kRows];
   int row[C::kPos + 1];                    // of a position (the general code's; -1: none)
-  int level[C::kRows];
+  int level[C::kRows];                     // general E: level of a row, and the columns it couples to
+  unsigned cols[C::kRows];
   int maxlevel;
   unsigned flags;
   union {
@@ -173,8 +187,19 @@ struct SolveShared {
       double G[C::kE][kNQ][kNQ];           // E* (lower part zeroed)
       double A[C::kE][3][kNQ][kNQ];        // -A^{j*}: the green update then adds Khat y
     } s;
-    R x[C::kBufs * C::kBuf + 2 * C::T * C::T];  // X of the chunks (+ what the last lanes' output reads may run over)
+    struct {
+      R x[C::kBufs * C::kBuf + 2 * C::T * C::T];  // X of the chunks (+ what the last lanes' output reads may run over)
+      double G[kInRows ? 1 : kCoupled];    // general E: the entries right of the diagonal, row by row
+    } c;
   } u;
+  __device__ __forceinline__ double* couplings() {
+    if constexpr (kInRows) return r.G;
+    else return u.c.G;
+  }
+  // entry (q, q + 1) of element e; (q, q + 1 + i) is i after it
+  __device__ __forceinline__ const double* coupling(int e, int q) {
+    return couplings() + e * (kNQ * (kNQ - 1) / 2) + q * (2 * kNQ - 1 - q) / 2;
+  }
 };
 
 // b += coefficient I of the 16 that the wave's register k holds, times y
@@ -264,7 +289,8 @@ __device__ __forceinline__ void wave_fence() {
 typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr unsigned kDenseStar = 1u, kGeneralE = 2u;
+constexpr unsigned kDenseStar = 1u, kGeneralE = 2u, kFarPartner = 4u;
+constexpr unsigned kColumns = (1u << kNQ) - 1, kClosed = 1u << 30, kStiff = 1u << 31;  // of SolveShared::cols
 
 // Algorithm 3 over a group of elements in precision R (the dark-blue solves
 // are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
@@ -297,6 +323,12 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   using LdsD = __attribute__((address_space(3))) double;
   constexpr int B = C::B, T = C::T, kE = C::kE, kThreads = C::kThreads, S = C::S, GW = C::GW, DN = C::DN, LN = C::LN;
   static_assert(zinv_columns<N>(), "two-entry rows of Z^-1");
+  // Modes of a chunk that the rounds of the late lanes take at a time, and time
+  // modes of a dense row in flight: as many as the rows of b leave registers
+  // for without a spill or a wave less per SIMD (N = 6, 16,384 elements, one
+  // coupling: 1,040 us with 3 modes, 870 with all).
+  constexpr bool kRoomy = 512 / STP_SOLVE_OCC - 2 * LN >= 128 && (sizeof(R) == 8 || STP_SOLVE_OCC <= 2);
+  constexpr int kPart = kRoomy ? C::kChunk : LN < 60 ? 3 : 2, kStep = !kRoomy ? 1 : sizeof(R) == 8 ? 2 : T;
   __shared__ SolveShared<N, R, Mode> sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -393,8 +425,6 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   const double gcoef = gmask ? sh.u.s.G[es][p][gp] : 0.0;
   const bool partner_coupled =
       group_mask<T>(grp, u, [&](int q) { return valid && gmask && q > gp && sh.u.s.G[es][gp][q] != 0.0; }) != 0;
-  const int ppos = gcount ? sh.pos[es * kNQ + gp] : pos;
-  (void)partner_coupled;
   // Row u of (Z - E*_pp I)^-1: two entries of Z^-1 without a diagonal source;
   // otherwise a dense row from an elimination, done only by waves holding
   // such a lane.  xc = row . S^-1 w.
@@ -437,7 +467,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
                                                                                         : 2);
   R sa0[kStarNnz], sa1[kStarNnz], sa2[kStarNnz];
   LdsR* sp[kStarNnz];
-  LdsR* const x0 = (LdsR*)&sh.u.x[0];
+  LdsR* const x0 = (LdsR*)&sh.u.c.x[0];
 #pragma unroll
   for (int k = 0; k < kStarNnz; ++k) {
     const bool live = mask != 0;
@@ -449,30 +479,50 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
     sa2[k] = live ? static_cast<R>(v2) : R(0);
     sp[k] = x0 + (live ? sh.pos[es * kNQ + q] : pos) * S + u;
   }
+  // A coupled lane is of the closure form (below), or late: its X follows in
+  // rounds after the others'.
+  const bool closed = gcount == 1 && !partner_coupled && z == 0.0, late = Mode != kResidual && gcount > 0 && !closed;
+  const int ppos = gcount > 0 && !late ? sh.pos[es * kNQ + gp] : pos;
+  if (u == 0 && valid) sh.cols[row] = gmask | (closed ? kClosed : 0u) | (z != 0.0 ? kStiff : 0u);
   {
-    const bool other_wave = ppos / GW != pos / GW;
     const unsigned f = (active && npop > kStarNnz ? kDenseStar : 0u) |
-                       (active && (gcount > 1 || (Mode != kResidual && gcount == 1 && (partner_coupled || other_wave || z != 0.0)))
-                            ? kGeneralE
-                            : 0u);
+                       (active && (Mode == kResidual ? gcount > 1 : late) ? kGeneralE : 0u) |
+                       (active && Mode != kResidual && ppos / GW != pos / GW ? kFarPartner : 0u);
     if (f) atomicOr(&sh.flags, f);
   }
   __syncthreads();
   const unsigned flags = __builtin_amdgcn_readfirstlane(sh.flags);
   const bool dense_star = (flags & kDenseStar) != 0, closure = (flags & kGeneralE) == 0;
-  if constexpr (Mode == kResidual) {
-  } else if (!closure) {
-    // dependency levels of a general upper-triangular E (level = longest
-    // coupling chain below a quantity), one thread per element
-    if (tid < nloc) {
+  // some coupled quantity's partner sits in another wave: barriers where the
+  // coupled quantities of a wave need only its own order
+  const bool far = (flags & kFarPartner) != 0;
+  if (__builtin_expect(!closure, 0)) {  // out of the way of the ordinary case, here and below
+    // The couplings of a general upper-triangular E move out of the setup's
+    // storage, which X takes: reading them from memory once per mode and time
+    // made such a workgroup 16 times as slow as an ordinary one (N = 6).
+    constexpr int kIt = (SolveShared<N, R, Mode>::kCoupled + kThreads - 1) / kThreads, kTri = kNQ * (kNQ - 1) / 2;
+    double gv[kIt];
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+      const int i = tid + k * kThreads, e = i / kTri;
+      int q = 0, o = i - e * kTri;  // row q, o places right of the diagonal
+#pragma unroll 1
+      for (; o >= kNQ - 1 - q; ++q) o -= kNQ - 1 - q;
+      gv[k] = e < kE ? sh.u.s.G[e][q][q + 1 + o] : 0.0;
+    }
+    // dependency levels (longest chain of late quantities down to a quantity),
+    // one thread per element
+    if (Mode != kResidual && tid < nloc) {
       int lev[kNQ];
       int mx = 0;
 #pragma unroll
       for (int o = kNQ - 1; o >= 0; --o) {
+        const unsigned m = sh.cols[tid * kNQ + o];
         int l = 0;
 #pragma unroll
         for (int q = o + 1; q < kNQ; ++q)
-          if (sh.u.s.G[tid][o][q] != 0.0 && lev[q] + 1 > l) l = lev[q] + 1;
+          if ((m >> q & 1u) && lev[q] + 1 > l) l = lev[q] + 1;
+        if (m & kClosed) l = 0;
         lev[o] = l;
         sh.level[tid * kNQ + o] = l;
         mx = l > mx ? l : mx;
@@ -480,17 +530,23 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
       atomicMax(&sh.maxlevel, mx);
     }
     __syncthreads();
-  } else if (wave_dense) {
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+      const int i = tid + k * kThreads;
+      if (i < SolveShared<N, R, Mode>::kCoupled) sh.couplings()[i] = gv[k];
+    }
+  }
+  if constexpr (Mode != kResidual) {
     // closure row of a coupled lane, X_o = Zinv_o (b_o + g X_p) = zr . b_o + dr . b_p:
     //   dr[w] = g sum_v (row u of Zinv_o)[v] Zinv_p[v][w],
-    // the rows Zinv_p[v] being those of the partner's lanes of this wave.
-    // After it a lane's dense row is: stiff lanes their row of Zinv (on their
-    // own b), coupled lanes dr (on the partner's b), the others zero.
+    // the rows Zinv_p[v] being those of the partner's lanes.  After it a
+    // lane's dense row is: stiff lanes their row of Zinv (on their own b),
+    // closed lanes dr (on the partner's b), the others zero.
     double r[T];
 #pragma unroll
     for (int w = 0; w < T; ++w) r[w] = 0.0;
-    if (gcount == 1) {
-      const int plane = wave * 64 + (ppos - wave * GW) * T;
+    if (closed) {
+      const int plane = ppos / GW * 64 + (ppos - ppos / GW * GW) * T;
 #pragma unroll
       for (int w = 0; w < T; ++w) {
         r[w] = gcoef * fma(zv0, sh.rows[plane + zc0][w], zv1 * sh.rows[plane + zc1][w]);
@@ -498,11 +554,18 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
       }
     }
     wave_fence();
-    if (z == 0.0) {
+    if (far) __syncthreads();
+    if (wave_dense) {
+      if (z == 0.0) {
 #pragma unroll
-      for (int w = 0; w < T; ++w) sh.rows[tid][w] = r[w];
-    } else {
-      zv0 = zv1 = 0.0;
+        for (int w = 0; w < T; ++w) sh.rows[tid][w] = r[w];
+      } else {
+        zv0 = zv1 = 0.0;
+      }
+    }
+    if (late) {  // in the top block the step below then leaves b = Q0 (S^-1 w) in place
+      xc = sinv_w(u);
+      dc = 0.0;
     }
   }
   // Rows of b below the top block (after the setup: its elimination needs the
@@ -532,6 +595,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
     for (int n = 0; n < LN; ++n)
       b[n] = static_cast<R>((n < kStaged ? (n < kFit ? s0[n] : s1[n - kFit]) : load_q0(n)) * w_u);
     wave_fence();
+    if (far) __syncthreads();  // Q0 of the partners
   } else {
 #pragma unroll
     for (int n = 0; n < LN; ++n) b[n] = static_cast<R>(load_r(n));
@@ -612,7 +676,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
         if constexpr (odd) {
           if (u == 0) xg[xb + c * T - 1] = xlast;
         }
-      } else if (Mode == kInit && g == N && closure) {
+      } else if (Mode == kInit && g == N) {
         if (wave_coupled) {
 #pragma unroll
           for (int k = 0; k < c; ++k)
@@ -625,58 +689,85 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
 #pragma unroll
         for (int k = 0; k < c; ++k) {
           if constexpr (g < N) xl[xb + k * T] = b[m0 + k];
-          else if constexpr (Mode == kInit) xl[xb + k * T] = static_cast<R>(qg[m0 - LN + k] * sinv_w(uc));
           else xl[xb + k * T] = rtop[k];
         }
         wave_fence();
-        if (closure) {
-          // columns of the two entries of a row of Z^-1: max(u - 1, 0), min(u + 1, N)
-          LdsR* const xz0 = xg + (uc > 0 ? uc - 1 : 0);
-          LdsR* const xz1 = xg + (uc < N ? uc + 1 : N);
-          double x[c];
+        if (far) __syncthreads();
+        // columns of the two entries of a row of Z^-1: max(u - 1, 0), min(u + 1, N)
+        LdsR* const xz0 = xg + (uc > 0 ? uc - 1 : 0);
+        LdsR* const xz1 = xg + (uc < N ? uc + 1 : N);
+        double x[c];
+#pragma unroll
+        for (int k = 0; k < c; ++k)
+          x[k] = fma(zv0, static_cast<double>(xz0[xb + k * T]), zv1 * static_cast<double>(xz1[xb + k * T]));
+        if (wave_dense) {
+          double r[T];
+#pragma unroll
+          for (int v = 0; v < T; ++v) r[v] = sh.rows[tid][v];
 #pragma unroll
           for (int k = 0; k < c; ++k)
-            x[k] = fma(zv0, static_cast<double>(xz0[xb + k * T]), zv1 * static_cast<double>(xz1[xb + k * T]));
-          if (wave_dense) {
-            double r[T];
 #pragma unroll
-            for (int v = 0; v < T; ++v) r[v] = sh.rows[tid][v];
-#pragma unroll
-            for (int k = 0; k < c; ++k)
-#pragma unroll
-              for (int v = 0; v < T; ++v) x[k] = fma(r[v], static_cast<double>(xs[xb + k * T + v]), x[k]);
-          }
-          wave_fence();
+            for (int v = 0; v < T; ++v) x[k] = fma(r[v], static_cast<double>(xs[xb + k * T + v]), x[k]);
+        }
+        wave_fence();
+        if (far) __syncthreads();
+        if (!late) {
 #pragma unroll
           for (int k = 0; k < c; ++k) xl[xb + k * T] = static_cast<R>(x[k]);
-        } else {
-          // level by level, in place: a lane reads its group's b and the X of
-          // the levels below, then the group's lanes overwrite b with X
-          const int row = sh.row[pos], es = row / kNQ, p = row - es * kNQ;
-          const int mylevel = active ? sh.level[row] : 0, maxlevel = __builtin_amdgcn_readfirstlane(sh.maxlevel);
+        }
+      }
+      if (Mode != kResidual && __builtin_expect(!closure, 0)) {
+        // late lanes, level by level: a lane adds the coupled quantities' X to
+        // its own value of b, still in its place, then the group's lanes
+        // exchange these sums (float64; through the group's block where it
+        // holds doubles) and overwrite b with X
+        const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? 0 : row - es * kNQ;
+        const int mine = active ? sh.level[row] : 0;
+        const unsigned cols = active ? sh.cols[row] : 0u;
+        const int maxlevel = __builtin_amdgcn_readfirstlane(sh.maxlevel);
 #pragma unroll 1
-          for (int lv = 0; lv <= maxlevel; ++lv) {
-            if (lv > 0) __syncthreads();
-            if (mylevel == lv) {
+        for (int lv = 1; lv <= maxlevel; ++lv) {
+          __syncthreads();
+          if (mine == lv) {
+            const bool dense = __builtin_amdgcn_ballot_w64((cols & kStiff) != 0) != 0;
+            static_for<0, (c + kPart - 1) / kPart>([&](auto part) __attribute__((always_inline)) {
+              constexpr int k0 = decltype(part)::value * kPart, kn = c - k0 < kPart ? c - k0 : kPart;
+              double sum[kn], x[kn];
+#pragma unroll
+              for (int k = 0; k < kn; ++k) sum[k] = static_cast<double>(xl[xb + (k0 + k) * T]);
+              const double* const gq = sh.coupling(es, p);
 #pragma unroll 1
-              for (int k = 0; k < c; ++k) {
-                double x = 0.0;
-#pragma unroll 1
-                for (int v = 0; v < T; ++v) {
-                  double acc = static_cast<double>(xg[xb + k * T + v]);
-                  if (lv > 0) {
-#pragma unroll 1
-                    for (int q = p + 1; q < kNQ; ++q) {
-                      const double gq = a.dt * a.E[((e0 + es) * kNQ + p) * kNQ + q];
-                      if (gq != 0.0) acc = fma(gq, static_cast<double>(x0[sh.pos[es * kNQ + q] * S + xb + k * T + v]), acc);
-                    }
-                  }
-                  x = fma(sh.rows[tid][v], acc, x);
-                }
-                wave_fence();
-                xl[xb + k * T] = static_cast<R>(x);
+              for (unsigned m = cols & kColumns; m != 0; m &= m - 1) {
+                const int q = __builtin_ctz(m);
+                const double gv = gq[q - p - 1];
+                LdsR* const xq = x0 + sh.pos[es * kNQ + q] * S + uc;
+#pragma unroll
+                for (int k = 0; k < kn; ++k) sum[k] = fma(gv, static_cast<double>(xq[xb + (k0 + k) * T]), sum[k]);
               }
-            }
+              if constexpr (sizeof(R) == 8) {
+#pragma unroll
+                for (int k = 0; k < kn; ++k) xl[xb + (k0 + k) * T] = sum[k];
+                wave_fence();
+              }
+              auto sum_of = [&](int k, int v) __attribute__((always_inline)) {  // of the group's lane v
+                if constexpr (sizeof(R) == 8) return xg[xb + (k0 + k) * T + v];
+                else return __shfl(sum[k], lane - uc + v);
+              };
+              const int v0 = uc > 0 ? uc - 1 : 0, v1 = uc < N ? uc + 1 : N;
+#pragma unroll
+              for (int k = 0; k < kn; ++k) x[k] = fma(zv0, sum_of(k, v0), zv1 * sum_of(k, v1));
+              if (dense) {
+#pragma unroll kStep
+                for (int v = 0; v < T; ++v) {
+                  const double r = sh.rows[tid][v];
+#pragma unroll
+                  for (int k = 0; k < kn; ++k) x[k] = fma(r, sum_of(k, v), x[k]);
+                }
+              }
+              wave_fence();
+#pragma unroll
+              for (int k = 0; k < kn; ++k) xl[xb + (k0 + k) * T] = static_cast<R>(x[k]);
+            });
           }
         }
       }
@@ -694,27 +785,33 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
         double zrow[T];  // row u of Z
 #pragma unroll
         for (int v = 0; v < T; ++v) zrow[v] = z_entry(uc, v);
-#pragma unroll
-        for (int k = 0; k < c; ++k) {
+        auto store_local = [&](int k, double ex) __attribute__((always_inline)) {  // ex: terms of E
           double base, zx = 0.0;
           if constexpr (g == N) base = qg[m0 - LN + k] * w_u;
           else base = b[m0 + k];
 #pragma unroll
           for (int v = 0; v < T; ++v) zx = fma(zrow[v], xg[xb + k * T + v], zx);
-          double ex = z * xl[xb + k * T];
-          if (closure) {
-            ex = fma(gcoef, xs[xb + k * T + uc], ex);
-          } else {
-            const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? kNQ : row - es * kNQ;
-            if (active) {
+          sh.r.res[pos * S + k * T + uc] = static_cast<float>(base - zx + ex);
+        };
+        if (__builtin_expect(closure, 1)) {
+#pragma unroll
+          for (int k = 0; k < c; ++k) store_local(k, fma(gcoef, xs[xb + k * T + uc], z * xl[xb + k * T]));
+        } else {
+          const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? 0 : row - es * kNQ;
+          double ex[c];
+#pragma unroll
+          for (int k = 0; k < c; ++k) ex[k] = z * xl[xb + k * T];
+          const double* const gq = sh.coupling(es, p);
 #pragma unroll 1
-              for (int q = p + 1; q < kNQ; ++q) {
-                const double gq = a.dt * a.E[((e0 + es) * kNQ + p) * kNQ + q];
-                if (gq != 0.0) ex = fma(gq, x0[sh.pos[es * kNQ + q] * S + xb + k * T + uc], ex);
-              }
-            }
+          for (unsigned m = active ? sh.cols[row] & kColumns : 0u; m != 0; m &= m - 1) {
+            const int q = __builtin_ctz(m);
+            const double gv = gq[q - p - 1];
+            LdsR* const xq = x0 + sh.pos[es * kNQ + q] * S + uc;
+#pragma unroll
+            for (int k = 0; k < c; ++k) ex[k] = fma(gv, xq[xb + k * T], ex[k]);
           }
-          sh.res[pos * S + k * T + uc] = static_cast<float>(base - zx + ex);
+#pragma unroll
+          for (int k = 0; k < c; ++k) store_local(k, ex[k]);
         }
         wave_fence();
       }
@@ -729,7 +826,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
         if constexpr (Mode == kResidual) {
           // four consecutive values per lane
           constexpr int n4 = c * T / 4, it4 = (n4 + T - 1) / T, rest = c * T - 4 * n4;
-          const float* const rg = sh.res + pos * S;
+          const float* const rg = sh.r.res + pos * S;
           char* const dst = Rb + roff - 4 * uc + m0 * (T * 4);
           if (active) {
 #pragma unroll
@@ -802,7 +899,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
           }
         };
         auto star = [&](auto k) __attribute__((always_inline)) {
-          if (!dense_star) {
+          if (__builtin_expect(!dense_star, 1)) {
             y0 = sa0[0] * xq[0];
             y1 = sa1[0] * xq[0];
             y2 = sa2[0] * xq[0];

@@ -1,0 +1,102 @@
+"""Forms of the source matrix that the solve kernel tells apart, one per
+workgroup of the build's tile table: a coupled quantity whose partner has no
+source of its own, in the partner's wave or in another (one element further); a
+quantity that is both stiff and coupled; a chain of two couplings; and a last
+workgroup of one ordinary element.  Expected values: the oracle; bar: the 1e-10
+per element and quantity of the parity tests."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import pool as opool  # noqa: E402
+from paper_2108_10565_amd import api  # noqa: E402
+from paper_2108_10565_amd import build as pbuild  # noqa: E402
+from paper_2108_10565_amd import workload as wl  # noqa: E402
+
+import parity  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-10
+PRECISIONS = {"fp64": dict(precision="fp64"), "fp32_refine2": dict(precision="fp32_refine", refine_steps=2)}
+_ORACLE = {}
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _make(nq, N, n, seed):
+    return wl.make_small(N, n, seed=seed) if nq == 13 else wl.make_maxwell(N, n, seed=seed)
+
+
+def _forms(nq, N):
+    """Workload, E and the elements that are checked (each form's and, next to
+    it, an ordinary one of the same workgroup)."""
+    elems = pbuild.solve_table(nq)[N][1]
+    n = 4 * elems + 1
+    w = _make(nq, N, n, 420 + N)
+    E, s = w.E.copy(), 1.0 / w.dt
+    a, b, c, d = 0, elems + 1, 2 * elems, 3 * elems
+    assert elems >= 2 and len({e // elems for e in (a, b, c, d, n - 1)}) == 5
+    far = 9 if nq == 13 else 4
+    for e in (a, b):
+        E[e, far, far] = 0.0
+        E[e, 0, 0] = 0.0
+        E[e, 0, far] = 0.3 * s
+    stiff, partner = (6, 10) if nq == 13 else (0, 5)
+    E[c, stiff, stiff], E[c, stiff, partner] = -2.0 * s, 0.4 * s
+    E[d, 3, 3] = E[d, 4, 4] = E[d, 5, 5] = 0.0
+    E[d, 3, 4], E[d, 4, 5] = 0.2 * s, -0.4 * s
+    return w, E, sorted({a, a + 1, b, b - 1, c, c + 1, d, d + 1, n - 1})
+
+
+@pytest.mark.parametrize("precision", list(PRECISIONS))
+@pytest.mark.parametrize("nq", [13, 6])
+@pytest.mark.parametrize("N", range(8))
+def test_one_form_per_workgroup(N, nq, precision):
+    print(f"[gpu] solve forms N={N} nq={nq} {precision}", flush=True)
+    w, E, ids = _forms(nq, N)
+    if (N, nq) not in _ORACLE:
+        _ORACLE[(N, nq)] = opool.solve_many(N, w.star[ids], E[ids], w.Q0[ids], w.dt)
+    Xo, Io = _ORACLE[(N, nq)]
+    Q, Qi = api.predict(_dev(w.Q0), _dev(w.star), _dev(E), w.dt, N, **PRECISIONS[precision])
+    torch.cuda.synchronize()
+    parity.check(Q.cpu().numpy()[ids], Xo, TOL, "Q")
+    parity.check(Qi.cpu().numpy()[ids], Io, TOL, "Qint")
+
+
+def _ms(call):
+    call()
+    best = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best.append(a.elapsed_time(b))
+    return min(best)
+
+
+@pytest.mark.parametrize("nq,N,n", [(13, 6, 16384), (13, 3, 65536), (6, 5, 32768)])
+def test_general_source_keeps_pace(nq, N, n):
+    """A level of couplings adds one round of exchange per chunk to the solve
+    of an ordinary E, no more than that solve itself: at most 1 + levels times
+    its time (it was 16 times for one level at N = 6, 150 times for twelve,
+    while the couplings were read from memory for every mode and time)."""
+    print(f"[gpu] general source pace nq={nq} N={N}", flush=True)
+    w = _make(nq, N, 64, 430 + N)
+    pick = torch.arange(n, device="cuda") % 64
+    star, Q0 = _dev(w.star)[pick].contiguous(), _dev(w.Q0)[pick].contiguous()
+    Q = torch.empty((n, nq, w.Q0.shape[2], N + 1), dtype=torch.float64, device="cuda")
+    Qi = torch.empty((n, nq, w.Q0.shape[2]), dtype=torch.float64, device="cuda")
+    one = w.E.copy()
+    one[:, 0, nq - 2] = 0.3 / w.dt
+    full = w.E + np.triu(np.full((nq, nq), 0.1 / w.dt), 1)
+    times = []
+    for E in (w.E, one, full):
+        Ed = _dev(E)[pick].contiguous()
+        times.append(_ms(lambda: api.predict(Q0, star, Ed, w.dt, N, Q=Q, Qint=Qi)))
+    print(f"  ordinary {times[0]:.3f} ms, one level {times[1]:.3f}, {nq - 1} levels {times[2]:.3f}", flush=True)
+    assert times[1] <= 2 * times[0] and times[2] <= nq * times[0]
