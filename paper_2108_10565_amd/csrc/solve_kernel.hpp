@@ -32,7 +32,9 @@
 // * Top block.  b = Q0 (S^-1 w) there, so X = Q0 (row of Zinv . S^-1 w) (and
 //   the same product with the closure row for a coupled quantity) is one or
 //   two products per value, without an exchange.
-// * Setup.  The columns of a star row are found with one ballot per group, a
+// * Setup.  Degree 0 has no green update and reads no star matrices (they
+//   were staged and scanned: 65,536 elements 92 -> 24 us, 100 elements 7.4 ->
+//   5.1).  The columns of a star row are found with one ballot per group, a
 //   lane's row of the dark-blue inverse by elimination and back substitution
 //   of one right-hand side, and Q0 is read once per group and staged through
 //   the group's X blocks (it was read again by each of the T lanes): N = 7,
@@ -106,7 +108,7 @@ struct SolveCfg {
 };
 
 // Which row (element * kNQ + quantity) each position holds, and back.  A
-// position without a row is -1.  Poroelastic rows are grouped by the length
+// position without a row is -1.  Here the poroelastic rows, grouped by the length
 // of their star row, which is uniform over most waves that way: normal
 // stresses and pressure (6 columns), then the velocity pairs (4; a pair never
 // straddles two waves, a shear row fills the gap), then the shear stresses
@@ -119,35 +121,45 @@ struct SolveLayout {
   constexpr SolveLayout() : row(), pos() {
     for (int i = 0; i < C::kPos; ++i) row[i] = -1;
     int next = 0;
-    if (kNQ == kNQPoro) {
-      const int wide[4] = {0, 1, 2, 9}, shear[3] = {3, 4, 5};
-      int filled = 0;  // shear rows placed so far
-      for (int k = 0; k < 4; ++k)
-        for (int e = 0; e < C::kE; ++e) row[next++] = static_cast<short>(e * kNQ + wide[k]);
-      for (int k = 0; k < 3; ++k)
-        for (int e = 0; e < C::kE; ++e) {
-          if (C::GW > 1 && next % C::GW == C::GW - 1) {
-            if (filled < 3 * C::kE) {
-              row[next] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
-              ++filled;
-            }
-            ++next;
+    const int wide[4] = {0, 1, 2, 9}, shear[3] = {3, 4, 5};
+    int filled = 0;  // shear rows placed so far
+    for (int k = 0; k < 4; ++k)
+      for (int e = 0; e < C::kE; ++e) row[next++] = static_cast<short>(e * kNQ + wide[k]);
+    for (int k = 0; k < 3; ++k)
+      for (int e = 0; e < C::kE; ++e) {
+        if (C::GW > 1 && next % C::GW == C::GW - 1) {
+          if (filled < 3 * C::kE) {
+            row[next] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
+            ++filled;
           }
-          row[next++] = static_cast<short>(e * kNQ + 6 + k);
-          row[next++] = static_cast<short>(e * kNQ + 10 + k);
+          ++next;
         }
-      for (; filled < 3 * C::kE; ++filled)
-        row[next++] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
-    } else {
-      for (int q = 0; q < kNQ; ++q)
-        for (int e = 0; e < C::kE; ++e) row[next++] = static_cast<short>(e * kNQ + q);
-    }
+        row[next++] = static_cast<short>(e * kNQ + 6 + k);
+        row[next++] = static_cast<short>(e * kNQ + 10 + k);
+      }
+    for (; filled < 3 * C::kE; ++filled)
+      row[next++] = static_cast<short>((filled % C::kE) * kNQ + shear[filled / C::kE]);
     for (int i = 0; i < C::kPos; ++i)
       if (row[i] >= 0) pos[row[i]] = static_cast<short>(i);
   }
 };
 template <int N>
 __device__ const SolveLayout<N> kSolveLayout{};
+
+// Row of a position and position of a row.  Any other system's order is
+// arithmetic: the table's latency would precede the loads of Q0 (6 quantities,
+// N = 2, 65,536 elements: 58 us with a table, 55 without).
+template <int N>
+__device__ __forceinline__ int layout_row(int pos) {
+  using C = SolveCfg<N, kInit>;
+  if constexpr (kNQ == kNQPoro) return kSolveLayout<N>.row[pos];
+  else return pos < C::kRows ? pos % C::kE * kNQ + pos / C::kE : -1;
+}
+template <int N>
+__device__ __forceinline__ int layout_pos(int row) {
+  if constexpr (kNQ == kNQPoro) return kSolveLayout<N>.pos[row];
+  else return row % kNQ * SolveCfg<N, kInit>::kE + row / kNQ;
+}
 
 template <int N>
 constexpr int khat_nnz() {
@@ -185,7 +197,7 @@ struct SolveShared {
   union {
     struct {                               // setup only
       double G[C::kE][kNQ][kNQ];           // E* (lower part zeroed)
-      double A[C::kE][3][kNQ][kNQ];        // -A^{j*}: the green update then adds Khat y
+      double A[N > 0 ? C::kE : 1][3][kNQ][kNQ];  // -A^{j*}: the green update then adds Khat y
     } s;
     struct {
       R x[C::kBufs * C::kBuf + 2 * C::T * C::T];  // X of the chunks (+ what the last lanes' output reads may run over)
@@ -337,15 +349,16 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   const int nloc = static_cast<int>(nloc64);
   const int grp = lane / T, u = lane - grp * T;
   const int pos = grp < GW ? wave * GW + grp : C::kPos;
-  const int row = grp < GW ? kSolveLayout<N>.row[pos] : -1;
+  const int row = grp < GW ? layout_row<N>(pos) : -1;
 
   // ---- setup: E, star and Khat to LDS (every load issued before the first
   // LDS store, so the group waits for one memory latency)
   constexpr int kEIt = (kE * kNQ * kNQ + kThreads - 1) / kThreads;
-  constexpr int kAIt = (3 * kE * kNQ * kNQ + kThreads - 1) / kThreads;
+  constexpr int kStar = N > 0 ? 3 * kE * kNQ * kNQ : 0;  // degree 0 has no green update
+  constexpr int kAIt = (kStar + kThreads - 1) / kThreads;
   constexpr int nnz = khat_nnz<N>(), kTab = SolveShared<N, R, Mode>::kTab, kKIt = (kTab + kThreads - 1) / kThreads;
   {
-    double ev[kEIt], av[kAIt];
+    double ev[kEIt], av[kAIt > 0 ? kAIt : 1];
     R kv[kKIt > 0 ? kKIt : 1];
     const R* const ktab = khat_sparse<N, R>();
 #pragma unroll
@@ -377,7 +390,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
 #pragma unroll
     for (int k = 0; k < kAIt; ++k) {
       const int i = tid + k * kThreads;
-      if (i < 3 * kE * kNQ * kNQ) (&sh.u.s.A[0][0][0][0])[i] = -(a.dt * av[k]);
+      if (i < kStar) (&sh.u.s.A[0][0][0][0])[i] = -(a.dt * av[k]);
     }
 #pragma unroll
     for (int k = 0; k < kKIt; ++k) {
@@ -385,7 +398,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
       if (i < kTab) sh.khat[i] = kv[k];
     }
   }
-  for (int i = tid; i < C::kRows; i += kThreads) sh.pos[i] = kSolveLayout<N>.pos[i];
+  for (int i = tid; i < C::kRows; i += kThreads) sh.pos[i] = layout_pos<N>(i);
   if (u == 0) sh.row[pos] = row;
   if (tid == 0) {
     sh.flags = 0;
@@ -457,9 +470,11 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   // sparse row p of the three star matrices: the columns with a non-zero in
   // any direction, in ascending order
   __builtin_amdgcn_sched_barrier(0);  // the elimination's registers are free before these are taken
-  unsigned mask = group_mask<T>(grp, u, [&](int q) {
-    return valid && (sh.u.s.A[es][0][p][q] != 0.0 || sh.u.s.A[es][1][p][q] != 0.0 || sh.u.s.A[es][2][p][q] != 0.0);
-  });
+  unsigned mask = 0;
+  if constexpr (N > 0)
+    mask = group_mask<T>(grp, u, [&](int q) {
+      return valid && (sh.u.s.A[es][0][p][q] != 0.0 || sh.u.s.A[es][1][p][q] != 0.0 || sh.u.s.A[es][2][p][q] != 0.0);
+    });
   const int npop = __builtin_popcount(mask);
   // columns the wave's longest row needs (wave-uniform: 2, 4 or 6)
   const int ns = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(npop > 4)   ? 6
@@ -469,7 +484,7 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   LdsR* sp[kStarNnz];
   LdsR* const x0 = (LdsR*)&sh.u.c.x[0];
 #pragma unroll
-  for (int k = 0; k < kStarNnz; ++k) {
+  for (int k = 0; N > 0 && k < kStarNnz; ++k) {
     const bool live = mask != 0;
     const int q = live ? __builtin_ctz(mask) : p;
     mask &= mask - 1;

@@ -100,3 +100,22 @@ def test_general_source_keeps_pace(nq, N, n):
         times.append(_ms(lambda: api.predict(Q0, star, Ed, w.dt, N, Q=Q, Qint=Qi)))
     print(f"  ordinary {times[0]:.3f} ms, one level {times[1]:.3f}, {nq - 1} levels {times[2]:.3f}", flush=True)
     assert times[1] <= 2 * times[0] and times[2] <= nq * times[0]
+
+
+@pytest.mark.parametrize("nq", [13, 6])
+def test_degree_zero_skips_the_star_matrices(nq):
+    """Degree 0 has no green update and does without the star matrices, which
+    are three quarters of its input: a large call takes less than half the time
+    of degree 1, which needs them and four times the degrees of freedom (it was
+    91 against 105 us, and 15.5 against 26, while degree 0 read them)."""
+    print(f"[gpu] degree 0 pace nq={nq}", flush=True)
+    n, times = 65536, []
+    for N in (0, 1):
+        w = _make(nq, N, 64, 440 + N)
+        pick = torch.arange(n, device="cuda") % 64
+        Q0, star, E = (_dev(a)[pick].contiguous() for a in (w.Q0, w.star, w.E))
+        Q = torch.empty((n, nq, w.Q0.shape[2], N + 1), dtype=torch.float64, device="cuda")
+        Qi = torch.empty((n, nq, w.Q0.shape[2]), dtype=torch.float64, device="cuda")
+        times.append(_ms(lambda: [api.predict(Q0, star, E, w.dt, N, Q=Q, Qint=Qi) for _ in range(20)]))
+    print(f"  degree 0 {times[0] / 20:.4f} ms, degree 1 {times[1] / 20:.4f}", flush=True)
+    assert times[0] < times[1] / 2
