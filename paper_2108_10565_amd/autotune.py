@@ -82,7 +82,7 @@ def build_variants(degrees, jobs: int | None = None, verbose: bool = True):
     def one(item):
         N, shape, obj = item
         try:
-            b._run(b.fused_object_cmd(N, tiles[N], shape, obj, 13))
+            b.compile_fused(b.fused_object_cmd(N, tiles[N], shape, obj, 13), obj)
         except RuntimeError as exc:
             return item, str(exc).splitlines()[-1][:200]
         others = [o for o in objs if os.path.basename(o) != b.fused_object_name(13, N)]

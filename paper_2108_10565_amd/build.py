@@ -4,7 +4,7 @@ Steps: (1) compile and run the host table generator (``csrc/gen_tables.cpp``
 + ``csrc/basis.cpp``), which writes ``csrc/generated/khat_tables.h``;
 (2) compile every ``.hip`` / ``.cpp`` source with hipcc for gfx950, one
 object per source (per quantity count and degree for the fused kernels, in
-parallel);
+parallel), and check each fused object's disassembly (``dpp_check.py``);
 (3) link ``paper_2108_10565_amd/libstp.so``.  The tile shape of each
 degree's fused kernels comes from ``tiles.json`` (written by ``autotune.py``).
 """
@@ -95,6 +95,17 @@ def fused_object_cmd(n: int, tile, solve, obj: str, nq: int = 13):
                                   os.path.join(CSRC, "kernel_fused.hip"), "-o", obj]
 
 
+def compile_fused(cmd, obj: str) -> str:
+    """Compiles one object of the fused kernels and checks its broadcasts."""
+    try:
+        from . import dpp_check
+    except ImportError:  # run as a script
+        import dpp_check
+    out = _run(cmd)
+    dpp_check.check(obj, ARCH)
+    return out
+
+
 def _objects():
     jobs = []
     for src in ("stp_api.hip", "kernel_ref.hip", "kernel_corrector.hip", "peaks.hip", "basis.cpp", "ader_host.cpp"):
@@ -118,7 +129,7 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     work = _objects()
     jobs = jobs or min(8, os.cpu_count() or 4)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        futs = [ex.submit(_run, cmd) for cmd, _ in work]
+        futs = [ex.submit(compile_fused, cmd, obj) if "kernel_fused" in obj else ex.submit(_run, cmd) for cmd, obj in work]
         for f in futs:
             out = f.result()
             if verbose and out.strip():

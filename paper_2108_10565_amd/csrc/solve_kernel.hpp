@@ -215,8 +215,11 @@ struct SolveShared {
 };
 
 // b += coefficient I of the 16 that the wave's register k holds, times y
-// (v_fmac with a row broadcast; k comes straight from an LDS read, so the
-// broadcast never follows a vector write of k).
+// (v_fmac with a row broadcast).  A broadcast needs two wait states after a
+// vector write of k, which the compiler does not insert for an asm operand.  k
+// comes straight from an LDS read, so there is no such write unless the
+// register allocator makes a copy; the build checks in the disassembly that it
+// made none (dpp_check.py).
 template <int I>
 __device__ __forceinline__ void fmac_bcast(double& b, double k, double y) {
   asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(b) : "v"(k), "v"(y), "n"(I));
