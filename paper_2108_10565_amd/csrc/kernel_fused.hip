@@ -66,8 +66,8 @@ constexpr int kMaxElems = 16;
 // Non-zero columns kept per lane of a star-matrix row (union over the three
 // directions).  The poroelastic Jacobians need at most 6 (normal-stress and
 // pressure rows couple to the 6 velocities; velocity rows to 3 stresses and
-// the pressure); a workgroup holding any row with more falls back to reading
-// the dense rows from global memory.
+// the pressure); for a row with more the solve kernel repeats the green update,
+// the matrix-core chain reads the dense rows from global memory.
 constexpr int kStarNnz = 6;
 
 template <int I>

@@ -48,8 +48,10 @@
 //   multiply-adds (the tile table of the build).
 //
 // Inputs outside the fast forms take further code in the same kernel, chosen
-// per workgroup.  A star row with more than kStarNnz columns reads the dense
-// rows from memory.  A coupled quantity of the closure form (one coupling, to
+// per workgroup.  Where a star row has more than kStarNnz columns, its wave
+// runs the green update again with the next ones, as the update is linear in
+// them (N = 4, 32,768 elements with one row of 13 columns: 555 us, 320 without;
+// 1,588 with the dense rows read from memory for every mode).  A coupled quantity of the closure form (one coupling, to
 // a quantity without couplings, and no source of its own) whose partner sits
 // in another wave costs two more barriers per chunk (N = 6, 16,384 elements
 // with one such coupling: 690 us, 695 without it).  Every other coupled
@@ -190,7 +192,7 @@ struct SolveShared {
   double q0[(C::kPos + 1) * C::DN];        // Q0 of the top block
   int pos[C::kRows];
   int row[C::kPos + 1];                    // of a position (the general code's; -1: none)
-  int level[C::kRows];                     // general E: level of a row, and the columns it couples to
+  int level[C::kRows];                     // level of a row (general E), and its columns (kColumns ..)
   unsigned cols[C::kRows];
   int maxlevel;
   unsigned flags;
@@ -305,7 +307,11 @@ typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr unsigned kDenseStar = 1u, kGeneralE = 2u, kFarPartner = 4u;
-constexpr unsigned kColumns = (1u << kNQ) - 1, kClosed = 1u << 30, kStiff = 1u << 31;  // of SolveShared::cols
+// of SolveShared::cols: the coupled columns, those of the star row above them
+// (at kStarShift), and
+constexpr unsigned kColumns = (1u << kNQ) - 1, kClosed = 1u << 30, kStiff = 1u << 31;
+constexpr int kStarShift = kNQ;
+static_assert(2 * kNQ <= 30, "the masks fit below the flags");
 
 // Algorithm 3 over a group of elements in precision R (the dark-blue solves
 // are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
@@ -478,11 +484,15 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
     mask = group_mask<T>(grp, u, [&](int q) {
       return valid && (sh.u.s.A[es][0][p][q] != 0.0 || sh.u.s.A[es][1][p][q] != 0.0 || sh.u.s.A[es][2][p][q] != 0.0);
     });
+  const unsigned star_mask = mask;
   const int npop = __builtin_popcount(mask);
   // columns the wave's longest row needs (wave-uniform: 2, 4 or 6)
-  const int ns = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(npop > 4)   ? 6
-                                                : __builtin_amdgcn_ballot_w64(npop > 2) ? 4
-                                                                                        : 2);
+  auto row_length = [](int n) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(n > 4)   ? 6
+                                          : __builtin_amdgcn_ballot_w64(n > 2) ? 4
+                                                                               : 2);
+  };
+  int ns = row_length(npop);
   R sa0[kStarNnz], sa1[kStarNnz], sa2[kStarNnz];
   LdsR* sp[kStarNnz];
   LdsR* const x0 = (LdsR*)&sh.u.c.x[0];
@@ -501,7 +511,8 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
   // rounds after the others'.
   const bool closed = gcount == 1 && !partner_coupled && z == 0.0, late = Mode != kResidual && gcount > 0 && !closed;
   const int ppos = gcount > 0 && !late ? sh.pos[es * kNQ + gp] : pos;
-  if (u == 0 && valid) sh.cols[row] = gmask | (closed ? kClosed : 0u) | (z != 0.0 ? kStiff : 0u);
+  if (u == 0 && valid)
+    sh.cols[row] = gmask | (star_mask << kStarShift) | (closed ? kClosed : 0u) | (z != 0.0 ? kStiff : 0u);
   {
     const unsigned f = (active && npop > kStarNnz ? kDenseStar : 0u) |
                        (active && (Mode == kResidual ? gcount > 1 : late) ? kGeneralE : 0u) |
@@ -917,70 +928,86 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
           }
         };
         auto star = [&](auto k) __attribute__((always_inline)) {
-          if (__builtin_expect(!dense_star, 1)) {
-            y0 = sa0[0] * xq[0];
-            y1 = sa1[0] * xq[0];
-            y2 = sa2[0] * xq[0];
-            auto add = [&](int i) __attribute__((always_inline)) {
-              y0 = fma(sa0[i], xq[i], y0);
-              y1 = fma(sa1[i], xq[i], y1);
-              y2 = fma(sa2[i], xq[i], y2);
-            };
-            add(1);
-            if (ns > 2) {
-              asm volatile("");
-              add(2);
-              add(3);
-            }
-            if (ns > 4) {
-              asm volatile("");
-              add(4);
-              add(5);
-            }
-          } else {
-            const int row = sh.row[pos], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? 0 : row - es * kNQ;
-            const double* st = a.star + (active ? e0 + es : e0) * (3 * kNQ * kNQ) + p * kNQ;
-            y0 = y1 = y2 = R(0);
-#pragma unroll 1
-            for (int q = 0; q < kNQ; ++q) {
-              const R xv = x0[sh.pos[es * kNQ + q] * S + uc + xb + decltype(k)::value * T];
-              y0 = fma(static_cast<R>(-(a.dt * st[q])), xv, y0);
-              y1 = fma(static_cast<R>(-(a.dt * st[kNQ * kNQ + q])), xv, y1);
-              y2 = fma(static_cast<R>(-(a.dt * st[2 * kNQ * kNQ + q])), xv, y2);
-            }
+          y0 = sa0[0] * xq[0];
+          y1 = sa1[0] * xq[0];
+          y2 = sa2[0] * xq[0];
+          auto add = [&](int i) __attribute__((always_inline)) {
+            y0 = fma(sa0[i], xq[i], y0);
+            y1 = fma(sa1[i], xq[i], y1);
+            y2 = fma(sa2[i], xq[i], y2);
+          };
+          add(1);
+          if (ns > 2) {
+            asm volatile("");
+            add(2);
+            add(3);
+          }
+          if (ns > 4) {
+            asm volatile("");
+            add(4);
+            add(5);
           }
         };
         // groups of 16 coefficients [G0, G1) of this chunk, kAhead in flight
         constexpr int kAhead = 2;
         constexpr int first = P::col_start[m0], last = P::col_start[m0 + c - 1] + P::col_count[m0 + c - 1];
         constexpr int G0 = first / 16, G1 = (last + 15) / 16;
-        R kc[kAhead + 1];
-        read_x(ic<0>{});
-        static_for<0, (kAhead < G1 - G0 ? kAhead : G1 - G0)>([&](auto i) __attribute__((always_inline)) {
-          kc[(G0 + decltype(i)::value) % (kAhead + 1)] = kl[(G0 + decltype(i)::value) * 16];
-        });
-        star(ic<0>{});
-        static_for<0, c>([&](auto k) __attribute__((always_inline)) {
-          constexpr int kk = decltype(k)::value, m = m0 + kk;
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (kk + 1 < c) read_x(ic<kk + 1>{});
-          static_for<0, P::col_count[m]>([&](auto i) __attribute__((always_inline)) {
-            constexpr int e = P::col_start[m] + decltype(i)::value, G = e / 16;
-            if constexpr ((e % 16 == 0 || e == first) && G + kAhead < G1) {
-              __builtin_amdgcn_sched_barrier(0);
-              kc[(G + kAhead) % (kAhead + 1)] = kl[(G + kAhead) * 16];
+        for (int pass = 0;; ++pass) {
+          R kc[kAhead + 1];
+          read_x(ic<0>{});
+          static_for<0, (kAhead < G1 - G0 ? kAhead : G1 - G0)>([&](auto i) __attribute__((always_inline)) {
+            kc[(G0 + decltype(i)::value) % (kAhead + 1)] = kl[(G0 + decltype(i)::value) * 16];
+          });
+          star(ic<0>{});
+          static_for<0, c>([&](auto k) __attribute__((always_inline)) {
+            constexpr int kk = decltype(k)::value, m = m0 + kk;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kk + 1 < c) read_x(ic<kk + 1>{});
+            static_for<0, P::col_count[m]>([&](auto i) __attribute__((always_inline)) {
+              constexpr int e = P::col_start[m] + decltype(i)::value, G = e / 16;
+              if constexpr ((e % 16 == 0 || e == first) && G + kAhead < G1) {
+                __builtin_amdgcn_sched_barrier(0);
+                kc[(G + kAhead) % (kAhead + 1)] = kl[(G + kAhead) * 16];
+                __builtin_amdgcn_sched_barrier(0);
+              }
+              constexpr int j = P::dir[e];
+              fmac_bcast<e % 16>(b[P::row[e]], kc[G % (kAhead + 1)], (j == 0) ? y0 : ((j == 1) ? y1 : y2));
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kk + 1 < c) star(ic<kk + 1>{});
+            if constexpr (C::kAlone && kk == 0) {
+              store_outputs();
               __builtin_amdgcn_sched_barrier(0);
             }
-            constexpr int j = P::dir[e];
-            fmac_bcast<e % 16>(b[P::row[e]], kc[G % (kAhead + 1)], (j == 0) ? y0 : ((j == 1) ? y1 : y2));
           });
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (kk + 1 < c) star(ic<kk + 1>{});
-          if constexpr (C::kAlone && kk == 0) {
-            store_outputs();
-            __builtin_amdgcn_sched_barrier(0);
+          if (kNQ <= kStarNnz || __builtin_expect(!dense_star, 1)) break;
+          // A longer star row: the update is linear in the columns, so the same
+          // code runs again with the next kStarNnz (as many times as the wave's
+          // longest row needs), then the first ones come back for the next chunk.
+          int po = pos;
+          asm volatile("" : "+v"(po));
+          const int row = sh.row[po], es = row < 0 ? 0 : row / kNQ, p = row < 0 ? 0 : row - es * kNQ;
+          unsigned cols = active ? sh.cols[row] >> kStarShift & kColumns : 0u;
+          const bool again = __builtin_amdgcn_ballot_w64(__builtin_popcount(cols) > (pass + 1) * kStarNnz) != 0;
+          constexpr bool kLast = g == 1 && cidx + 1 == nchunks(g, C::kChunk);
+          if (!again && (pass == 0 || kLast)) break;
+          for (int k = again ? (pass + 1) * kStarNnz : 0; k > 0; --k) cols &= cols - 1;
+          ns = row_length(__builtin_popcount(cols));
+          const char* const Sb = reinterpret_cast<const char*>(a.star + e0 * (3 * kNQ * kNQ));
+          const unsigned soff = active ? 8u * ((es * 3 * kNQ + p) * kNQ) : 0u;
+#pragma unroll
+          for (int k = 0; k < kStarNnz; ++k) {
+            const int q = cols != 0 ? __builtin_ctz(cols) : p;
+            const double f = cols != 0 ? -a.dt : 0.0;
+            cols &= cols - 1;
+            const unsigned off = soff + 8u * q;
+            sa0[k] = static_cast<R>(f * *reinterpret_cast<const double*>(Sb + off));
+            sa1[k] = static_cast<R>(f * *reinterpret_cast<const double*>(Sb + off + 8 * kNQ * kNQ));
+            sa2[k] = static_cast<R>(f * *reinterpret_cast<const double*>(Sb + off + 16 * kNQ * kNQ));
+            sp[k] = x0 + (f != 0.0 ? sh.pos[es * kNQ + q] : po) * S + u;
           }
-        });
+          if (!again) break;
+        }
       }
       if constexpr (!green || !C::kAlone) store_outputs();
     });

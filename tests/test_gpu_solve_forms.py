@@ -1,9 +1,10 @@
-"""Forms of the source matrix that the solve kernel tells apart, one per
-workgroup of the build's tile table: a coupled quantity whose partner has no
+"""Forms of the source and star matrices that the solve kernel tells apart, one
+per workgroup of the build's tile table: a coupled quantity whose partner has no
 source of its own, in the partner's wave or in another (one element further); a
-quantity that is both stiff and coupled; a chain of two couplings; and a last
-workgroup of one ordinary element.  Expected values: the oracle; bar: the 1e-10
-per element and quantity of the parity tests."""
+quantity that is both stiff and coupled; a chain of two couplings; star rows of
+more than six columns; and a last workgroup of one ordinary element.  Expected
+values: the oracle where not said otherwise; bar: the 1e-10 per element and
+quantity of the parity tests.  What each form may cost is bounded as well."""
 import numpy as np
 import pytest
 
@@ -66,6 +67,37 @@ def test_one_form_per_workgroup(N, nq, precision):
     parity.check(Qi.cpu().numpy()[ids], Io, TOL, "Qint")
 
 
+@pytest.mark.parametrize("precision", list(PRECISIONS))
+@pytest.mark.parametrize("N", [1, 3, 6, 7])
+def test_star_rows_of_every_length(N, precision):
+    """One star row of 6, 7, 12 or 13 columns in a workgroup of its own (the
+    kernel takes six at a time), next to ordinary elements, and a workgroup of
+    rows of every length.  Expected values: the one-element-per-workgroup
+    reference kernel, which applies the same block elimination; such rows let
+    the solution grow by up to 1e24, where the oracle's dense solve has no
+    digit left."""
+    print(f"[gpu] star rows N={N} {precision}", flush=True)
+    elems = pbuild.solve_table(13)[N][1]
+    w = wl.make_small(N, 5 * elems + 1, seed=460 + N)
+    star, rng = w.star.copy(), np.random.default_rng(461 + N)
+
+    def fill(e, row, columns):
+        star[e, :, row, :] = 0.0
+        pick = rng.permutation(13)[:columns]
+        star[e][:, row, pick] = rng.standard_normal((3, columns)) * np.abs(w.star[e]).max() * 1e-3
+
+    for g, columns in enumerate((6, 7, 12, 13)):
+        fill(g * elems + g % elems, (3 * g + 1) % 13, columns)
+    for row in range(13):
+        fill(4 * elems, row, row + 1)
+    args = (_dev(w.Q0), _dev(star), _dev(w.E), w.dt, N)
+    Xr, Ir = api.predict(*args, reference_kernel=True)
+    Q, Qi = api.predict(*args, **PRECISIONS[precision])
+    torch.cuda.synchronize()
+    parity.check(Q.cpu().numpy(), Xr.cpu().numpy(), TOL, "Q")
+    parity.check(Qi.cpu().numpy(), Ir.cpu().numpy(), TOL, "Qint")
+
+
 def _ms(call):
     call()
     best = []
@@ -119,3 +151,24 @@ def test_degree_zero_skips_the_star_matrices(nq):
         times.append(_ms(lambda: [api.predict(Q0, star, E, w.dt, N, Q=Q, Qint=Qi) for _ in range(20)]))
     print(f"  degree 0 {times[0] / 20:.4f} ms, degree 1 {times[1] / 20:.4f}", flush=True)
     assert times[0] < times[1] / 2
+
+
+@pytest.mark.parametrize("N,n", [(3, 65536), (4, 32768), (6, 16384)])
+def test_long_star_rows_keep_pace(N, n):
+    """A star row of 13 columns takes three passes of the green update: at most
+    three times the ordinary time (it was 4 to 5 times while the dense rows were
+    read from memory for every mode)."""
+    print(f"[gpu] long star rows pace N={N}", flush=True)
+    w = wl.make_small(N, 64, seed=470 + N)
+    pick = torch.arange(n, device="cuda") % 64
+    Q0, E = _dev(w.Q0)[pick].contiguous(), _dev(w.E)[pick].contiguous()
+    Q = torch.empty((n, 13, w.Q0.shape[2], N + 1), dtype=torch.float64, device="cuda")
+    Qi = torch.empty((n, 13, w.Q0.shape[2]), dtype=torch.float64, device="cuda")
+    longer = w.star.copy()
+    longer[:, :, 4, :] += np.random.default_rng(471).standard_normal((64, 3, 13)) * np.abs(w.star).max() * 1e-3
+    times = []
+    for star in (w.star, longer):
+        sd = _dev(star)[pick].contiguous()
+        times.append(_ms(lambda: api.predict(Q0, sd, E, w.dt, N, Q=Q, Qint=Qi)))
+    print(f"  ordinary {times[0]:.3f} ms, one row of 13 columns {times[1]:.3f}", flush=True)
+    assert times[1] <= 3 * times[0]
