@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "launch_slices.hpp"
 
 namespace stp {
 namespace {
@@ -59,14 +60,14 @@ __device__ __forceinline__ v4d mfma(double a, double b, v4d c) {
 // accumulator register r of lane l is row l / 16 + 4 r, column l % 16.
 //
 // TPW: output tiles (16 modes) per wave; an element takes
-// ceil(NT / TPW) waves.
+// ceil(NT / TPW) waves.  block0: first workgroup of this launch's slice.
 template <int NQ, int N, int TPW>
-__global__ __launch_bounds__(256, 2) void corrector_kernel(CorrectArgs a) {
+__global__ __launch_bounds__(256, 2) void corrector_kernel(CorrectArgs a, int64_t block0) {
   constexpr int B = n_modes(N), QB = NQ * B, Q2 = NQ * NQ, BB = B * B;
   constexpr int NT = (B + 15) / 16, kParts = (NT + TPW - 1) / TPW, QS = (NQ + 3) / 4, kTerms = 11;
   const int lane = threadIdx.x % 64, col = lane % 16, kq = lane / 16;
   const int64_t unit =
-      static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+      (block0 + blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int64_t e = unit / kParts;
   if (e >= a.n) return;
   const int c0 = kParts > 1 ? static_cast<int>(unit % kParts) * TPW : 0;  // first output tile of this wave
@@ -239,9 +240,10 @@ template <int NQ, int N, int TPW>
 hipError_t launch_tiles(const CorrectArgs& a, hipStream_t stream) {
   constexpr int NT = (n_modes(N) + 15) / 16, kParts = (NT + TPW - 1) / TPW;
   const int64_t blocks = (a.n * kParts + 3) / 4;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((corrector_kernel<NQ, N, TPW>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, a);
-  return hipGetLastError();
+  return for_slices(blocks, 256, hipSuccess, [&](int64_t first, unsigned count) {
+    hipLaunchKernelGGL((corrector_kernel<NQ, N, TPW>), dim3(count), dim3(256), 0, stream, a, first);
+    return hipGetLastError();
+  });
 }
 
 // Output tiles per wave.  W is formed once per wave and term (4 instructions
