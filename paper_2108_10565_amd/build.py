@@ -6,7 +6,8 @@ Steps: (1) compile and run the host table generator (``csrc/gen_tables.cpp``
 object per source (per quantity count and degree for the fused kernels, in
 parallel), and check each fused object's disassembly (``dpp_check.py``);
 (3) link ``paper_2108_10565_amd/libstp.so``.  The tile shape of each
-degree's fused kernels comes from ``tiles.json`` (written by ``autotune.py``).
+degree's fused kernels comes from ``tiles.json`` (the solve kernel's shapes as
+``autotune.py`` keeps them by its measurements, which are in that file).
 """
 from __future__ import annotations
 
@@ -69,7 +70,7 @@ def tile_table(path: str = TILES) -> dict:
 def solve_table(nq: int, path: str = TILES) -> dict:
     """{degree: (waves, elements, chunk, waves per SIMD, X buffers, chunk of the
     correction and the residual)} of the solve kernel for nq quantities, as the
-    autotuner wrote it."""
+    autotuner keeps it."""
     import json
     t = json.load(open(path))["solve"][str(nq)]
     return {int(n): tuple(int(x) for x in v) for n, v in t.items()}
