@@ -63,7 +63,7 @@ CANDIDATES = {
         7: [(8, 10, 3, 2, 2, 3), (8, 10, 7, 2, 1, 3), (8, 10, 8, 2, 1, 3)]}}
 ELEMENTS = {0: 262144, 1: 262144, 2: 262144, 3: 131072, 4: 65536, 5: 65536, 6: 32768, 7: 16384}
 POOL = 384          # generated elements the timed ones are gathered from
-KEPT_WITHIN = 0.03
+KEPT_WITHIN = 0.015
 # paths: (precision, refinement steps, bound of the relative difference between
 # two shapes' outputs: their sums run in another order)
 PATHS = {"float64": (0, 0, 1e-12), "float32 chain": (1, 0, 1e-2), "float32, 1 refinement": (1, 1, 1e-8)}
