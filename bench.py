@@ -151,8 +151,10 @@ def measured_traffic(workload: str):
     """HBM bytes per launch of the float64 fused kernel from the committed
     counter summary (FETCH_SIZE + WRITE_SIZE of one dispatch, each scaled by
     the ratio measured on a plain device copy), or None if the summary is
-    missing or was taken on other kernel sources."""
+    missing or was taken on other kernel sources or another tile."""
     import hashlib
+
+    from paper_2108_10565_amd import build as pbuild
     path = os.path.join(ROOT, "profiles", f"traffic_fused_fp64_{workload}.json")
     if not os.path.exists(path):
         return None
@@ -160,7 +162,7 @@ def measured_traffic(workload: str):
     sha = hashlib.sha256()
     for name in ("kernel_fused.hip", "solve_kernel.hpp"):
         sha.update(open(os.path.join(ROOT, "paper_2108_10565_amd", "csrc", name), "rb").read())
-    if sha.hexdigest() != rec.get("kernel_sources_sha256"):
+    if sha.hexdigest() != rec.get("kernel_sources_sha256") or list(pbuild.solve_table(13)[6]) != rec.get("tile"):
         return None
     return rec["hbm_bytes_per_launch"]
 

@@ -225,8 +225,8 @@ def main(argv=None):
     ap.add_argument("phase", choices=["build", "measure"])
     ap.add_argument("--nq", type=int, nargs="+", default=sorted(CANDIDATES, reverse=True), choices=sorted(CANDIDATES))
     ap.add_argument("--degrees", type=int, nargs="+", default=list(range(0, 8)))
-    ap.add_argument("--out", default=os.path.join(ROOT, "gpurun_out"),
-                    help="directory of the measured tiles.json (copy it over paper_2108_10565_amd/tiles.json)")
+    ap.add_argument("--out", default=TUNE_DIR,
+                    help="directory of the measured tiles.json (copy it over the package's)")
     ap.add_argument("--jobs", type=int, default=None)
     args = ap.parse_args(argv)
     if args.phase == "build":

@@ -24,10 +24,11 @@
 //      dr = G_op (row of Zinv_o) Zinv_p, so no extra round is needed; any
 //      other coupled quantity follows level by level (level = longest
 //      coupling chain below it);
-//   2. outputs: X to Q and dt X[:, :, 0] to Qint;
-//   3. green blocks: every lane reads X[q, m, u] of the quantities in its
+//   2. green blocks: every lane reads X[q, m, u] of the quantities in its
 //      star row, forms y_1..y_3 with its row of A^{1*}, A^{2*}, A^{3*}, and
-//      subtracts Khat^j[n, m] y_j from its registers b[n].
+//      subtracts Khat^j[n, m] y_j from its registers b[n];
+//   3. outputs: X to Q and dt X[:, :, 0] to Qint (the matrix-core chain and a
+//      tile that fills the compute unit issue them earlier).
 // A^{j*} = dt A^j and E* = dt E are formed in-kernel, so every product runs
 // with unit scaling (the paper's libxsmm alpha = 1 remark, section "Roofline
 // model").
@@ -54,8 +55,7 @@ static_assert(supported_nq(kNQ), "quantity count without kernels");
 
 // Tile shape of the matrix-core chain: threads per workgroup (upper bound; rounded to
 // whole elements and waves) and modes per chunk (degree blocks are split
-// evenly).  Both come from the build, which takes them from the table the
-// autotuner writes after timing every candidate shape on the device.
+// evenly).  Both come from the build, which takes them from its tile table.
 #if !defined(STP_TILE_THREADS) || !defined(STP_TILE_CHUNK)
 #error "compile with -DSTP_TILE_THREADS=T -DSTP_TILE_CHUNK=C (the tile table of the build)"
 #endif
@@ -208,10 +208,8 @@ __device__ __forceinline__ void zt_solve(double z, const double (&rhs)[T], doubl
   for (int r = 0; r < T; ++r) out[r] = a[r][T];
 }
 
-// The usage-ordered Khat table of degree N in precision R.  Kernels pass its
-// address through an empty asm statement before reading it, so the compiler
-// cannot fold the values into instruction literals and reads them with
-// scalar loads instead.
+// The usage-ordered Khat table of degree N in precision R (the solve kernel
+// copies it to LDS).
 template <int N, typename R>
 __device__ __forceinline__ const R* khat_sparse() {
   if constexpr (sizeof(R) == 8) {

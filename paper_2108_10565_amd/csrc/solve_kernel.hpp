@@ -4,12 +4,13 @@
 //
 // What bounds it.  At N = 6 an element needs 1.0 MFLOP on the float64 vector
 // pipe (14.6 ns at the measured 70 TFLOP/s) and moves 84 KB (16.8 ns at the
-// measured 5 TB/s copy), so neither alone explains the 39 ns it takes (50 ns
+// measured 5 TB/s copy), so neither alone explains the 37 ns it takes (50 ns
 // with scalar-loaded Khat and workgroup-wide dark-blue steps): with one or two
 // waves per SIMD the time goes to latencies that nothing overlaps (scalar
 // loads of Khat, workgroup barriers, LDS round trips of the dark-blue step).
-// Of a workgroup's 117,000 cycles the green update takes 65,000 (43,000 at the
-// pipe's rate), X and its barriers 26,000, the setup 24,000.
+// Of a workgroup's 117,000 cycles (at 39 ns, while the code of the dense star
+// rows stood in every mode) the green update took 65,000 (43,000 at the pipe's
+// rate), X and its barriers 26,000, the setup 24,000.
 // The layout below is chosen to keep those latencies short:
 //
 // * Columns.  One lane per right-hand-side column (element e, quantity p,
@@ -93,7 +94,9 @@ struct SolveCfg {
   // buffer takes a second barrier, but twice the modes fit, so there are half
   // as many exchanges (N = 3, 262,144 elements: float64 1.21 against 1.24 ms,
   // float32 chain 1.02 against 1.18; N = 5, 262,144: 4.68 against 4.95 with 9
-  // modes instead of 3; N = 7 keeps two, 1.43 against 1.72 at 16,384).
+  // modes instead of 3; N = 7 with 13 quantities, 16,384: 1.42 with 6 modes
+  // against 1.46 with 4 in two buffers, 1.72 against 1.43 while the code of the
+  // dense star rows stood in every mode).
   static constexpr int kBufs = Mode == kInit ? STP_SOLVE_BUFS : 2;
   static constexpr int kChunkTile = Mode == kInit ? STP_SOLVE_CHUNK : STP_SOLVE_CHUNK2;
   static constexpr int kChunk = kChunkTile < DN ? kChunkTile : DN;
@@ -313,6 +316,19 @@ constexpr unsigned kColumns = (1u << kNQ) - 1, kClosed = 1u << 30, kStiff = 1u <
 constexpr int kStarShift = kNQ;
 static_assert(2 * kNQ <= 30, "the masks fit below the flags");
 
+// Waves per SIMD the registers are held to.  The residual keeps about 30 more
+// than the solve (X of the next chunk, a row of Z), so where the rows of b leave
+// no more than 100 it gets one wave less (N = 5) unless its workgroup needs all
+// of them (N = 7: 8 waves, 2 per SIMD; it spills there, 232 registers with 13
+// quantities and 145 with six, and with the chain and the correction still takes
+// 2.3 ms at 8,192 elements with one refinement, against 5.2 ms for the residual
+// kernel with one wave per SIMD and no spill).
+template <int N, int Mode>
+constexpr int solve_occupancy() {
+  using C = SolveCfg<N, Mode>;
+  return Mode == kResidual && C::kWaves <= 4 && 512 / STP_SOLVE_OCC - 2 * C::LN <= 100 ? STP_SOLVE_OCC - 1 : STP_SOLVE_OCC;
+}
+
 // Algorithm 3 over a group of elements in precision R (the dark-blue solves
 // are float64 in every mode).  kInit: b = Q0 (S^-1 w), Q <- X.  kCorrect:
 // b = the residual in `work` (float), Q <- Q + X.
@@ -326,15 +342,6 @@ static_assert(2 * kNQ <= 30, "the masks fit below the flags");
 // update applied to the known X, chunk by chunk from the top block down, so it
 // shares that code; X comes from Q one chunk ahead instead of from the
 // dark-blue step, and the local terms of a chunk's rows follow its barrier.
-// waves per SIMD the registers are held to: the residual keeps about 30 more
-// than the solve (X of the next chunk, a row of Z), so it gets one wave less
-// where they would spill (N = 5)
-template <int N, int Mode>
-constexpr int solve_occupancy() {
-  using C = SolveCfg<N, Mode>;
-  return Mode == kResidual && C::kWaves <= 4 && 512 / STP_SOLVE_OCC - 2 * C::LN <= 100 ? STP_SOLVE_OCC - 1 : STP_SOLVE_OCC;
-}
-
 template <int N, typename R, int Mode>
 __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, Mode>())) void solve_kernel(PredictArgs a, float* work) {
   using C = SolveCfg<N, Mode>;
@@ -845,8 +852,8 @@ __global__ __launch_bounds__((SolveCfg<N, Mode>::kThreads), (solve_occupancy<N, 
         wave_fence();
       }
       // ---- outputs of the chunk from the group's own block: Q <- X or
-      // Q <- Q + X, and Qint = dt X[:, :, 0] (the block lives until the chunk
-      // after the next).  Issued after the green update, where the lane has
+      // Q <- Q + X, and Qint = dt X[:, :, 0] (only the group writes its block,
+      // and not before its next X in the same buffer).  Issued after the green update, where the lane has
       // registers to spare, except where one workgroup fills the compute unit:
       // its waves would all be storing at once there, with no one's
       // multiply-adds to cover it (N = 6: 2.73 ms against 2.67 ms after the
